@@ -203,7 +203,7 @@ static void do_prepare(const cola_params& p, cola_state* st, const Bufs& b, hipS
   const auto& tp = twiddles(b.L.np);
   COLA_HIP_CHECK(hipMemcpyAsync(b.tw_m, tm.data(), tm.size() * sizeof(float2), hipMemcpyHostToDevice, s));
   COLA_HIP_CHECK(hipMemcpyAsync(b.tw_p, tp.data(), tp.size() * sizeof(float2), hipMemcpyHostToDevice, s));
-  launch_growth_ode(p, b.L, b.growth, b.ref, s);
+  launch_growth_ode(p, b.L, b.growth, b.ref, b.pk_scratch, s);   // the P(k) scratch is free here
   for (int i = 0; i < p.n_steps; ++i) launch_write_step(b.steps, i, step_dev(p, b.L, i), s);
   st->prepared = 1;
 }

@@ -360,7 +360,8 @@ Layout make_layout(const cola_params& p) {
   L.off_tw_p = o;
   o = align_up(o + (size_t)L.np * sizeof(float2));
   L.off_scratch = o;
-  L.scratch_bytes = pk_scratch_bytes(L, 2048) + align_up(2048 * (sizeof(float4) + 8));
+  L.scratch_bytes = std::max(pk_scratch_bytes(L, 2048) + align_up(2048 * (sizeof(float4) + 8)),
+                             growth_scratch_bytes(p));
   o = align_up(o + L.scratch_bytes);
   L.off_lpt_coef = o;
   o = align_up(o + (L.kdep ? 2 * (size_t)L.n_k * sizeof(float2) : 0));

@@ -5,9 +5,9 @@
 //   D2'' = kappa mu D2 - kappa mu D1^2 [1 + 2 a^4 H^2 gamma_2(k, k/sqrt2, k/sqrt2, a)/(kappa mu)],
 // primes d/dtau, kappa = 1.5 Omega_m a, with the Einstein-de Sitter growing-mode values at
 // a_ini (D1 = 1, D1' = a^2 E, D2 = -3/7, D2' = -(6/7) a^2 E).  One thread integrates one
-// integer |nu|^2 of the particle grid (k = 2 pi |nu| / L) with classical fourth-order
-// Runge-Kutta in ln a (steps <= 1e-3), stopping exactly on every a_i of the time grid.
-// This is the only double-precision arithmetic on the device.
+// integer |nu|^2 of the particle grid (k = 2 pi |nu| / L) in ln a with steps that end
+// exactly on every a_i of the time grid (eighth-order extrapolation, see the growth tables
+// below); the triangle solver takes classical fourth-order Runge-Kutta steps <= 1e-3.
 //
 // Initial field: counter-based SplitMix64 white noise (Steele, Lea & Flood 2014) with a
 // Box-Muller transform, scaled in Fourier space by sqrt(N P_ini(k) / L^3), where P_ini is
@@ -215,59 +215,166 @@ __device__ __forceinline__ void growth_model(const GrowthDev& g, const MBSpline&
   }
 }
 
-// d y / d ln a for y = (D1, D1', D2, D2'), ' = d/dtau; d/dln a = (a^2 E)^-1 d/dtau.
-// HALF (the COLA_READ_D2_HALF_K reading): y also carries (D1, D1') at k/sqrt2, and the D2
-// source takes that D1 squared in place of D1(k)^2.
-template <bool HALF>
-__device__ __forceinline__ void growth_rhs(const GrowthDev& g, const MBSpline& mb, double k, double lna,
-                                           const double* y, double* dy) {
+// ------------------------------------------------------------------ growth tables
+// y = (D1, D1', D2, D2') per |nu|^2, ' = d/dtau, integrated in ln a by Gragg-Bulirsch-Stoer
+// steps of order 8: modified midpoint with 2, 4, 6 and 8 substeps over the same step,
+// extrapolated in the substep squared.  Every sequence needs the right-hand side at
+// rational points of the step only, and at a point the equations depend on the mode through
+// k^2 alone:
+//   mu = mu_0 + c_1 k^2/(k^2 + m),  gamma_2 term = s + G k^2/((k^2 + m)(k^2/2 + m)^2)
+// with m = a^2 m^2 (no mode dependence where c_1 = G = 0).  So k_growth_nodes evaluates the
+// model's functions of a once per point, for all modes, and k_growth_ode reads them from
+// LDS: two reciprocals and about thirty FP64 operations per mode and point.
+//
+// What bounds it: up to about 10^5 modes (a wave or two per SIMD) the latency of one mode's
+// chain of steps, so few, wide steps whose four sequences advance independently; above
+// that the FP64 rate.  Measured on a whole table: 10.2 -> 0.24 ms for the 769 modes of 32^3
+// particles and 18.6 -> 0.41 ms for the 110593 of 384^3 (f(R), from z = 19, 10 and 30
+// slices), against fourth-order Runge-Kutta steps of 1e-3 that evaluated the model in full
+// for every mode and stage.  Steps of 0.04 hold the largest relative error of any table
+// entry at 1e-13 (the Runge-Kutta steps: 4e-13); it is truncation from 0.05 on, rounding
+// below.
+constexpr double kGrowthStep = 0.04;     // longest step in ln a
+constexpr double kGradeFirst = 1e-10;    // after a_*: steps kGradeFirst + kGrade (ln a - ln a_*)
+constexpr double kGrade = 0.1;           // (error 3e-13; 0.2 gives 7e-13, 0.3 1e-11)
+constexpr int kGrowthNodes = 13;         // points of a step: 0 ... 7/8 of the sequences, and 1
+constexpr int kGrowthChunk = 128;        // steps per k_growth_nodes launch (kernel arguments)
+constexpr int kGrowthRound = 16;         // steps staged in LDS at a time
+
+// Functions of a at one point, each times f = d tau / d ln a where it multiplies y:
+// y_0' = f y_1, y_1' = q y_0 with q = A + B k^2 R, and the D2 source (q + g) y_0^2 with
+// g = s + G k^2 R Q^2, R = 1/(k^2 + m), Q = 1/(k^2/2 + m).  kap: f kappa (LCDM's q).
+// ext: the step length (point 0) and the slice written after the step, or -1 (point 12).
+struct __align__(16) GrowthNode {
+  double f, kap, A, B, m, s, G, ext;
+};
+
+// Consecutive steps: step j runs from l[j] to l[j + 1] in ln a.
+struct GrowthSteps {
+  int n, first;
+  double l[kGrowthChunk + 1];
+  int16_t out[kGrowthChunk];
+};
+
+__device__ __forceinline__ GrowthNode growth_node(const GrowthDev& g, const MBSpline& mb, double lna) {
   const double a = exp(lna);
-  double mu, g2t;
-  growth_model(g, mb, k, a, mu, g2t);
-  const double kap = 1.5 * g.om * a;
-  const double f = 1.0 / (a * a * dE(a, g.om));
-  const double ds = HALF ? y[4] : y[0];
-  dy[0] = y[1] * f;
-  dy[1] = kap * mu * y[0] * f;
-  dy[2] = y[3] * f;
-  dy[3] = (kap * mu * y[2] - kap * mu * ds * ds - g2t * ds * ds) * f;
-  if constexpr (HALF) {
-    dy[4] = y[5] * f;
-    dy[5] = kap * growth_mu(g, mb, k * M_SQRT1_2, a) * y[4] * f;
+  const double E = dE(a, g.om);
+  const double f = 1.0 / (a * a * E), kap = 1.5 * g.om * a;
+  const double ah = a * kH0c, ah2 = ah * ah, a3 = a * a * a;
+  double mu0 = 1.0, c1 = 0.0, m = 1.0, s = 0.0, G = 0.0;
+  if (g.model == COLA_FR_HS1) {
+    const double ol = 1.0 - g.om;
+    const double X = g.om / a3 + 4.0 * ol, Y = g.om + 4.0 * ol;
+    const double r = X / Y;
+    m = ah2 * Y * r * r * r / (2.0 * g.fr0);
+    c1 = 1.0 / 3.0;
+    // gamma_2^E (Sec. 5.1): the c_0 of its Pi(k) = k^2/(a H0)^2 + c_0 is m/(a H0)^2
+    G = -18.0 * g.om * g.om * a / (48.0 * a3 * g.fr0 * g.fr0) * (X * X * X * X * X) / (Y * Y * Y * Y) * ah2 * ah2;
+  } else if (g.model == COLA_NDGP) {
+    const double oma = g.om / a3 / (E * E);
+    const double beta = 1.0 + 2.0 * g.rc * E * (1.0 - 0.5 * oma);
+    mu0 = 1.0 + 1.0 / (3.0 * beta);
+    s = -(g.rc * g.rc * g.om * g.om) / (3.0 * beta * beta * beta * a * a);
+  } else if (g.model == COLA_KMOUFLAGE) {   // gamma_2 = 0
+    mu0 = growth_mu(g, mb, 0.0, a);
+  } else if (g.model == COLA_MBETA || (g.model == COLA_SYMMETRON && a > g.sa)) {
+    double b2, m2, dm2;   // beta^2, m^2/H0^2 and its derivative in a
+    if (g.model == COLA_MBETA) {
+      double b;
+      mb_eval(mb, a, b, m2, dm2);
+      b2 = b * b;
+    } else {
+      const double r = g.sa / a, sv = 1.0 - r * r * r;
+      b2 = g.sb * g.sb * sv;
+      m2 = g.sm * g.sm * sv;
+      dm2 = g.sm * g.sm * 3.0 * g.sa * g.sa * g.sa / (a * a3);
+    }
+    m = ah2 * m2;
+    c1 = 2.0 * b2;
+    G = m2 * dm2 * b2 * g.om * ah2 * ah2 * ah2 / (kH0c * kH0c);
   }
+  return GrowthNode{f, f * kap, f * kap * mu0, f * kap * c1, m, f * s, f * G, 0.0};
 }
 
+__global__ void __launch_bounds__(64)
+k_growth_nodes(GrowthDev g, MBSpline mb, GrowthSteps st, GrowthNode* __restrict__ nodes) {
+  constexpr double at[kGrowthNodes] = {0.0,     1.0 / 8, 1.0 / 6, 1.0 / 4, 1.0 / 3, 3.0 / 8, 1.0 / 2,
+                                       5.0 / 8, 2.0 / 3, 3.0 / 4, 5.0 / 6, 7.0 / 8, 1.0};
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  const int j = e / kGrowthNodes, i = e % kGrowthNodes;
+  if (j >= st.n) return;
+  const double l0 = st.l[j], l1 = st.l[j + 1], h = l1 - l0;
+  GrowthNode nd = growth_node(g, mb, i + 1 == kGrowthNodes ? l1 : l0 + at[i] * h);
+  if (i == 0) nd.ext = h;
+  if (i + 1 == kGrowthNodes) nd.ext = (double)st.out[j];
+  nodes[(int64_t)(st.first + j) * kGrowthNodes + i] = nd;
+}
+
+// One mode's coefficients at a point; HALF (the COLA_READ_D2_HALF_K reading): y also
+// carries (D1, D1') at k/sqrt2, whose q is qh, and the D2 source takes that D1 squared in
+// place of D1(k)^2.
 template <bool HALF>
-__device__ __forceinline__ void store_slice(const GrowthDev& g, const MBSpline& mb, double k, double a,
-                                            const double* y, double* out) {
-  double mu, g2t;
-  growth_model(g, mb, k, a, mu, g2t);
-  const double kap = 1.5 * g.om * a;
+struct GrowthMode {
+  double f, q, g, qh;
+  __device__ __forceinline__ GrowthMode(const GrowthNode& n, double k2, bool ref) {
+    const double R = 1.0 / (k2 + n.m), Q = 1.0 / (0.5 * k2 + n.m);
+    f = n.f;
+    q = ref ? n.kap : n.A + n.B * (k2 * R);
+    g = ref ? 0.0 : n.s + n.G * (k2 * R) * (Q * Q);
+    qh = HALF ? (ref ? n.kap : n.A + n.B * (0.5 * k2 * Q)) : 0.0;
+  }
+  // zm + h y'(z)
+  __device__ __forceinline__ void midpoint(double* zm, double* z, double h) const {
+    const double ds = HALF ? z[4] : z[0];
+    const double d[4] = {f * z[1], q * z[0], f * z[3], q * z[2] - (q + g) * (ds * ds)};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double t = zm[v] + h * d[v];
+      zm[v] = z[v];
+      z[v] = t;
+    }
+    if constexpr (HALF) {
+      const double t4 = zm[4] + h * (f * z[5]), t5 = zm[5] + h * (qh * z[4]);
+      zm[4] = z[4];
+      zm[5] = z[5];
+      z[4] = t4;
+      z[5] = t5;
+    }
+  }
+};
+
+// one slice of the table from the state y at the point of `nd`
+template <bool HALF>
+__device__ __forceinline__ void growth_store(const GrowthNode& nd, double k2, bool ref, const double* y,
+                                             double* out) {
+  const GrowthMode<HALF> c(nd, k2, ref);
   const double ds = HALF ? y[4] : y[0];
+  const double tau = 1.0 / c.f;   // D'' is per tau
   out[0] = y[0];
   out[1] = y[1];
-  out[2] = kap * mu * y[0];
+  out[2] = c.q * tau * y[0];
   out[3] = y[2];
   out[4] = y[3];
-  out[5] = kap * mu * y[2] - kap * mu * ds * ds - g2t * ds * ds;
+  out[5] = (c.q * y[2] - (c.q + c.g) * (ds * ds)) * tau;
 }
 
+// Thread t integrates |nu|^2 = t (t == n_k: the LCDM reference of the initial spectrum, of
+// which only the state at a = 1 is kept).  The substep points of the four sequences are
+// visited in ascending order, so that each point's coefficients are formed once and used
+// by every sequence that has a substep there.
 template <bool HALF>
-__global__ void __launch_bounds__(64) k_growth_ode(GrowthDev g, MBSpline mb, double* __restrict__ table,
-                                                   double* __restrict__ ref) {
+__global__ void __launch_bounds__(64)
+k_growth_ode(GrowthDev g, const GrowthNode* __restrict__ nodes, int nsteps, double* __restrict__ table,
+             double* __restrict__ ref_out) {
+  constexpr int NV = HALF ? 6 : 4, NS = 4;
+  // extrapolation weights prod_{i != j} n_j^2/(n_j^2 - n_i^2) of n = 2, 4, 6, 8
+  constexpr double wt[NS] = {-1.0 / 360.0, 16.0 / 45.0, -729.0 / 280.0, 1024.0 / 315.0};
+  __shared__ GrowthNode nd[kGrowthRound * kGrowthNodes];
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t > g.n_k) return;
-  GrowthDev gg = g;
-  double k;
-  if (t == g.n_k) {   // LCDM reference for the initial spectrum: D1(a = 1), mu = 1
-    gg.model = COLA_LCDM;
-    k = 0.0;
-  } else {
-    k = g.kdep ? g.kf * sqrt((double)t) : 0.0;
-  }
+  const bool ref = t >= g.n_k, store = t < g.n_k;
+  const double k2 = (ref || !g.kdep) ? 0.0 : g.kf * g.kf * (double)t;
   const double ai = g.a_ini;
   const double g0 = ai * ai * dE(ai, g.om);
-  constexpr int NV = HALF ? 6 : 4;
   double y[NV];
   y[0] = 1.0;
   y[1] = g0;
@@ -277,21 +384,62 @@ __global__ void __launch_bounds__(64) k_growth_ode(GrowthDev g, MBSpline mb, dou
     y[4] = 1.0;
     y[5] = g0;
   }
-  double lna = log(ai);
-  const int nsl = (t == g.n_k) ? 1 : g.n_steps + 1;
-  for (int i = 0; i < nsl; ++i) {
-    const double a_target = (t == g.n_k) ? 1.0 : ai + i * (1.0 - ai) / g.n_steps;
-    const double l1 = log(a_target);
-    rk4_to_knots<NV>(y, lna, l1, growth_kink(gg), gg, mb,
-                     [&](double l, const double* yy, double* dy) { growth_rhs<HALF>(gg, mb, k, l, yy, dy); });
-    if (t == g.n_k)
-      store_slice<HALF>(gg, mb, k, a_target, y, ref);
-    else
-      store_slice<HALF>(gg, mb, k, a_target, y, table + ((int64_t)i * g.n_k + t) * 6);
+  for (int s0 = 0; s0 < nsteps; s0 += kGrowthRound) {
+    const int ns = nsteps - s0 < kGrowthRound ? nsteps - s0 : kGrowthRound;
+    __syncthreads();   // the previous round's points have been read
+    {
+      constexpr int V = sizeof(GrowthNode) / sizeof(double2);
+      const double2* src = reinterpret_cast<const double2*>(nodes + (int64_t)s0 * kGrowthNodes);
+      double2* dst = reinterpret_cast<double2*>(nd);
+      for (int e = threadIdx.x; e < ns * kGrowthNodes * V; e += blockDim.x) dst[e] = src[e];
+    }
+    __syncthreads();
+    if (s0 == 0 && store) growth_store<HALF>(nd[0], k2, ref, y, table + t * 6);
+    for (int s = 0; s < ns; ++s) {
+      const GrowthNode* p = nd + s * kGrowthNodes;
+      const double H = p[0].ext;
+      double zm[NS][NV], z[NS][NV];
+#pragma unroll
+      for (int j = 0; j < NS; ++j)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) zm[j][v] = z[j][v] = y[v];
+      // sequence j (2 j + 2 substeps) from point i to its next one; the first substep is an
+      // Euler step of half the midpoint's length
+      auto sub = [&](int i, int j, const GrowthMode<HALF>& c) {
+        const double h = H / (double)(2 * j + 2);
+        c.midpoint(zm[j], z[j], i == 0 ? h : 2.0 * h);
+      };
+      // sequences with a substep at each point (bit j: 2 j + 2 substeps)
+      constexpr int who[kGrowthNodes - 1] = {15, 8, 4, 2 | 8, 4, 8, 15, 8, 4, 2 | 8, 4, 8};
+#pragma unroll
+      for (int i = 0; i < kGrowthNodes - 1; ++i) {
+        const GrowthMode<HALF> c(p[i], k2, ref);
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+          if ((who[i] >> j) & 1) sub(i, j, c);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) y[v] = (wt[0] * z[0][v] + wt[1] * z[1][v]) + (wt[2] * z[2][v] + wt[3] * z[3][v]);
+      const int out = (int)p[kGrowthNodes - 1].ext;   // uniform over the work-group
+      if (out >= 0 && store) growth_store<HALF>(p[kGrowthNodes - 1], k2, ref, y, table + ((int64_t)out * g.n_k + t) * 6);
+    }
+    if (t == g.n_k && s0 + ns == nsteps) growth_store<HALF>(nd[ns * kGrowthNodes - 1], k2, ref, y, ref_out);
   }
 }
 
-void launch_growth_ode(const cola_params& p, const Layout& L, double* table, double* ref,
+// Step boundaries in ln a: every a_i, the knots of a tabulated {m, beta} model (the splines'
+// third derivatives jump there) and the symmetron's a_* are boundaries.  Just after a_*
+// the symmetron's gamma_2 term has a peak whose width in ln a scales as (k / (a_* m_*))^2,
+// far below kGrowthStep for the fundamental mode of a large box, so the steps there start
+// at kGradeFirst and grow by kGrade per step.
+size_t growth_scratch_bytes(const cola_params& p) {
+  const double graded = std::log(kGrowthStep / kGradeFirst) / std::log1p(kGrade);
+  const double span = std::min(std::log1p(p.z_init), 710.0);   // ln of the largest double
+  const double steps = span / kGrowthStep + p.n_steps + COLA_MBETA_MAX_KNOTS + graded + 8;
+  return (size_t)steps * kGrowthNodes * sizeof(GrowthNode);
+}
+
+void launch_growth_ode(const cola_params& p, const Layout& L, double* table, double* ref, void* scratch,
                        hipStream_t s) {
   ProfScope ps("growth_ode", s);
   GrowthDev g;
@@ -312,14 +460,64 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
   g.kdep = L.kdep ? 1 : 0;
   g.n_steps = p.n_steps;
   g.n_k = L.n_k;
-  const int64_t threads = L.n_k + 1;
   const MBSpline mb = mb_spline(p);
+  GrowthNode* nodes = static_cast<GrowthNode*>(scratch);
+  int nsteps = 0;
+  GrowthSteps st;
+  st.n = st.first = 0;
+  auto flush = [&] {
+    if (st.n == 0) return;
+    const int e = st.n * kGrowthNodes;
+    hipLaunchKernelGGL(k_growth_nodes, dim3((e + 63) / 64), dim3(64), 0, s, g, mb, st, nodes);
+    COLA_LAUNCH_CHECK();
+    st.first += st.n;
+    st.n = 0;
+  };
+  auto step = [&](double l0, double l1, int out) {
+    st.l[st.n] = l0;
+    st.l[st.n + 1] = l1;
+    st.out[st.n++] = (int16_t)out;
+    ++nsteps;
+    if (st.n == kGrowthChunk) flush();
+  };
+  // [l0, l1] in equal steps of at most kGrowthStep; the last one writes slice `out`
+  auto uniform = [&](double l0, double l1, int out) {
+    const int n = (int)std::min(std::max(1.0, std::ceil((l1 - l0) / kGrowthStep)), 710.0 / kGrowthStep);
+    const double h = (l1 - l0) / n;
+    for (int j = 0; j < n; ++j)
+      step(l0 + j * h, j + 1 == n ? l1 : l0 + (j + 1) * h, j + 1 == n ? out : -1);
+  };
+  const double kink = g.model == COLA_SYMMETRON ? std::log(p.sym_astar) : 0.0;
+  const bool graded = g.model == COLA_SYMMETRON;
+  double lna = std::log(g.a_ini);
+  for (int i = 1; i <= p.n_steps; ++i) {
+    const double l1 = std::log(a_of_step(p, i));
+    if (g.model == COLA_MBETA)
+      for (int j = 0; j < mb.n; ++j)
+        if (mb.x[j] > lna && mb.x[j] < l1) {
+          uniform(lna, mb.x[j], -1);
+          lna = mb.x[j];
+        }
+    if (graded && lna < kink && kink < l1) {
+      uniform(lna, kink, -1);
+      lna = kink;
+    }
+    if (graded && lna >= kink)
+      for (;;) {
+        const double h = kGradeFirst + kGrade * (lna - kink);
+        if (h >= kGrowthStep || h >= l1 - lna) break;
+        step(lna, lna + h, -1);
+        lna += h;
+      }
+    uniform(lna, l1, i);
+    lna = l1;
+  }
+  flush();
+  const dim3 grid((unsigned)((L.n_k + 1 + 63) / 64)), block(64);
   if (p.readings & COLA_READ_D2_HALF_K)
-    hipLaunchKernelGGL(k_growth_ode<true>, dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s, g,
-                       mb, table, ref);
+    hipLaunchKernelGGL(k_growth_ode<true>, grid, block, 0, s, g, nodes, nsteps, table, ref);
   else
-    hipLaunchKernelGGL(k_growth_ode<false>, dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s, g,
-                       mb, table, ref);
+    hipLaunchKernelGGL(k_growth_ode<false>, grid, block, 0, s, g, nodes, nsteps, table, ref);
   COLA_LAUNCH_CHECK();
 }
 

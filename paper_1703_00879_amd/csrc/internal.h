@@ -288,7 +288,9 @@ void fft_autotune(const FFTPlan& pl, float2* data, hipStream_t s, int out[2]);
 
 // ------------------------------------------------------------------ kernels (launchers)
 void launch_fill(float* p, size_t n, float v, hipStream_t s);
-void launch_growth_ode(const cola_params& p, const Layout& L, double* table, double* ref,
+// growth tables (ref: the LCDM state at a = 1); scratch holds growth_scratch_bytes(p)
+size_t growth_scratch_bytes(const cola_params& p);
+void launch_growth_ode(const cola_params& p, const Layout& L, double* table, double* ref, void* scratch,
                        hipStream_t s);
 // exact D2 of triangles tri[i] = (k, k1, k2) and D2_hat(k)(1 - cos^2 theta) at a into
 // out[i] = (exact, approximation); NaN for sets that are no triangle
