@@ -498,7 +498,7 @@ cola_status cola_make_ic(const cola_params* p, cola_state* st, hipStream_t s) {
     launch_noise(*p, L.np, L.pitch_p, L.plane_p, R(M[0]), nullptr, s);
     fft_r2c(pp, R(M[0]), M[0], s);
     float2* phi1 = L.kdep ? b.phi1 : M[1];
-    launch_ic_phi1(*p, L, M[0], phi1, sigma8_norm(*p), b.ref, s);
+    launch_ic_phi1(*p, L, M[0], phi1, b.ref, s);
     // 2LPT source S = sum_{i<j} phi_ii phi_jj - phi_ij^2 (eq. lcdm2lpt)
     for (int c = 0; c < 3; ++c) {
       KOp op = base;

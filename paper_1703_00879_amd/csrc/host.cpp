@@ -3,8 +3,6 @@
 // * background: flat LCDM, E(a) = sqrt(Om a^-3 + 1 - Om), d tau = da/(a^3 E) (Sec. 2);
 // * time grid: a_i uniform in a from a_ini to 1; kick/drift intervals in tau by
 //   Gauss-Legendre quadrature;
-// * initial spectrum: Eisenstein & Hu (1998) no-wiggle transfer function, normalised to
-//   sigma8 by Gauss-Legendre quadrature in ln k over 1e-5 < k < 1e2 h/Mpc;
 // * PM-force scalars of the models at a given a (Secs. 5-6).
 
 #include <algorithm>
@@ -84,33 +82,6 @@ double tau_between(const Cosmo& c, double a0, double a1) {
 double a_of_step(const cola_params& p, int i) {
   const double ai = 1.0 / (1.0 + p.z_init);
   return ai + i * (1.0 - ai) / p.n_steps;
-}
-
-// ------------------------------------------------------------------ initial spectrum
-double eh_transfer(const cola_params& p, double k) {
-  const double theta = p.t_cmb / 2.7;
-  const double omh2 = p.omega_m * p.h * p.h, obh2 = p.omega_b * p.h * p.h;
-  const double fb = p.omega_b / p.omega_m;
-  const double s = 44.5 * std::log(9.83 / omh2) / std::sqrt(1.0 + 10.0 * std::pow(obh2, 0.75));
-  const double alpha = 1.0 - 0.328 * std::log(431.0 * omh2) * fb + 0.38 * std::log(22.3 * omh2) * fb * fb;
-  const double ks = 0.43 * k * p.h * s;
-  const double gam = p.omega_m * p.h * (alpha + (1.0 - alpha) / (1.0 + ks * ks * ks * ks));
-  const double q = k * theta * theta / gam;
-  const double L0 = std::log(2.0 * M_E + 1.8 * q);
-  const double C0 = 14.2 + 731.0 / (1.0 + 62.5 * q);
-  return L0 / (L0 + C0 * q * q);
-}
-
-double sigma8_norm(const cola_params& p) {
-  auto f = [&](double lnk) {
-    const double k = std::exp(lnk);
-    const double x = 8.0 * k;
-    const double W = x > 1e-4 ? 3.0 * (std::sin(x) - x * std::cos(x)) / (x * x * x) : 1.0 - x * x / 10.0;
-    const double T = eh_transfer(p, k);
-    return k * k * k * std::pow(k, p.n_s) * T * T * W * W / (2.0 * M_PI * M_PI);
-  };
-  const double I = integrate(f, std::log(1e-5), std::log(1e2), 4000);
-  return p.sigma8 * p.sigma8 / I;
 }
 
 // ------------------------------------------------------------------ general {m, beta} tables
@@ -354,7 +325,7 @@ Layout make_layout(const cola_params& p) {
   L.off_growth = o;
   o = align_up(o + (size_t)(p.n_steps + 1) * L.n_k * 6 * sizeof(double));
   L.off_ref = o;
-  o = align_up(o + 6 * sizeof(double));
+  o = align_up(o + 7 * sizeof(double));
   L.off_tw_m = o;
   o = align_up(o + (size_t)L.nm * sizeof(float2));
   L.off_tw_p = o;

@@ -358,14 +358,73 @@ __device__ __forceinline__ void growth_store(const GrowthNode& nd, double k2, bo
   out[5] = (c.q * y[2] - (c.q + c.g) * (ds * ds)) * tau;
 }
 
+// Eisenstein & Hu (1998) no-wiggle spectrum in double precision: constants of k^ns T(k)^2.
+struct SpecDev {
+  double ns, th2, omh, alpha, kfac, s8;   // th2 = (T_CMB/2.7 K)^2, kfac = 0.43 s h (s in Mpc)
+  __device__ __forceinline__ double power(double k) const {
+    const double kk = kfac * k;
+    const double k4 = (kk * kk) * (kk * kk);
+    const double gam = omh * (alpha + (1.0 - alpha) / (1.0 + k4));
+    const double q = k * th2 / gam;
+    const double L0 = log(2.0 * 2.718281828459045235 + 1.8 * q);
+    const double C0 = 14.2 + 731.0 / (1.0 + 62.5 * q);
+    const double T = L0 / (L0 + C0 * q * q);
+    return pow(k, ns) * T * T;
+  }
+};
+
+// A with sigma8^2 = A int d ln k k^3/(2 pi^2) k^ns T^2 W(8 k)^2 over 1e-5 < k < 1e2 h/Mpc, by
+// 16-point Gauss-Legendre panels: kSpecLow equal ones in ln k up to kSpecSplit, then kSpecHigh
+// equal ones in k, whose 8 rad of the top-hat's phase each keeps the rule converged (relative
+// error 1e-14).  One wave, a panel node per lane and turn.
+constexpr int kSpecLow = 64, kSpecHigh = 96;
+constexpr double kSpecSplit = 0.5;
+__device__ __forceinline__ double sigma8_norm(const SpecDev& sp) {
+  constexpr double gx[8] = {0.09501250983763745, 0.2816035507792589, 0.45801677765722737,
+                            0.6178762444026438,  0.755404408355003,  0.8656312023878318,
+                            0.9445750230732326,  0.9894009349916499};
+  constexpr double gw[8] = {0.18945061045506859, 0.1826034150449236,  0.16915651939500262,
+                            0.14959598881657676, 0.12462897125553403, 0.09515851168249259,
+                            0.062253523938647706, 0.027152459411754037};
+  const double l0 = log(1e-5), lm = log(kSpecSplit);
+  double sum = 0.0;
+  for (int e = (int)threadIdx.x; e < (kSpecLow + kSpecHigh) * 16; e += 64) {
+    const int pnl = e >> 4, n = e & 7;
+    double a, b;   // the panel in ln k
+    if (pnl < kSpecLow) {
+      a = l0 + pnl * ((lm - l0) / kSpecLow);
+      b = l0 + (pnl + 1) * ((lm - l0) / kSpecLow);
+    } else {
+      const double dk = (1e2 - kSpecSplit) / kSpecHigh;
+      a = log(kSpecSplit + (pnl - kSpecLow) * dk);
+      b = log(kSpecSplit + (pnl - kSpecLow + 1) * dk);
+    }
+    const double x = (e & 8) ? gx[n] : -gx[n];
+    const double k = exp(0.5 * (a + b) + 0.5 * (b - a) * x);
+    const double y = 8.0 * k;
+    const double W = y > 1e-4 ? 3.0 * (sin(y) - y * cos(y)) / (y * y * y) : 1.0 - y * y / 10.0;
+    sum += 0.5 * (b - a) * gw[n] * (k * k * k * sp.power(k) * W * W);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  return sp.s8 * sp.s8 * (2.0 * M_PI * M_PI) / sum;
+}
+
 // Thread t integrates |nu|^2 = t (t == n_k: the LCDM reference of the initial spectrum, of
 // which only the state at a = 1 is kept).  The substep points of the four sequences are
 // visited in ascending order, so that each point's coefficients are formed once and used
-// by every sequence that has a substep there.
+// by every sequence that has a substep there.  The last work-group computes the spectrum's
+// normalisation into ref_out[6] meanwhile: it is done well before the tables, and the host,
+// whose own quadrature took 4-5 ms a run, only launches.
 template <bool HALF>
 __global__ void __launch_bounds__(64)
-k_growth_ode(GrowthDev g, const GrowthNode* __restrict__ nodes, int nsteps, double* __restrict__ table,
-             double* __restrict__ ref_out) {
+k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int nsteps,
+             double* __restrict__ table, double* __restrict__ ref_out) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    const double A = sigma8_norm(sp);
+    if (threadIdx.x == 0) ref_out[6] = A;
+    return;
+  }
   constexpr int NV = HALF ? 6 : 4, NS = 4;
   // extrapolation weights prod_{i != j} n_j^2/(n_j^2 - n_i^2) of n = 2, 4, 6, 8
   constexpr double wt[NS] = {-1.0 / 360.0, 16.0 / 45.0, -729.0 / 280.0, 1024.0 / 315.0};
@@ -432,6 +491,21 @@ k_growth_ode(GrowthDev g, const GrowthNode* __restrict__ nodes, int nsteps, doub
 // the symmetron's gamma_2 term has a peak whose width in ln a scales as (k / (a_* m_*))^2,
 // far below kGrowthStep for the fundamental mode of a large box, so the steps there start
 // at kGradeFirst and grow by kGrade per step.
+static SpecDev spec_dev(const cola_params& p) {
+  SpecDev e;
+  const double omh2 = p.omega_m * p.h * p.h, obh2 = p.omega_b * p.h * p.h;
+  const double fb = p.omega_b / p.omega_m;
+  const double sh = 44.5 * std::log(9.83 / omh2) / std::sqrt(1.0 + 10.0 * std::pow(obh2, 0.75));
+  const double th = p.t_cmb / 2.7;
+  e.ns = p.n_s;
+  e.th2 = th * th;
+  e.omh = p.omega_m * p.h;
+  e.alpha = 1.0 - 0.328 * std::log(431.0 * omh2) * fb + 0.38 * std::log(22.3 * omh2) * fb * fb;
+  e.kfac = 0.43 * sh * p.h;
+  e.s8 = p.sigma8;
+  return e;
+}
+
 size_t growth_scratch_bytes(const cola_params& p) {
   const double graded = std::log(kGrowthStep / kGradeFirst) / std::log1p(kGrade);
   const double span = std::min(std::log1p(p.z_init), 710.0);   // ln of the largest double
@@ -513,11 +587,12 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
     lna = l1;
   }
   flush();
-  const dim3 grid((unsigned)((L.n_k + 1 + 63) / 64)), block(64);
+  const SpecDev sp = spec_dev(p);
+  const dim3 grid((unsigned)((L.n_k + 1 + 63) / 64) + 1), block(64);
   if (p.readings & COLA_READ_D2_HALF_K)
-    hipLaunchKernelGGL(k_growth_ode<true>, grid, block, 0, s, g, nodes, nsteps, table, ref);
+    hipLaunchKernelGGL(k_growth_ode<true>, grid, block, 0, s, g, sp, nodes, nsteps, table, ref);
   else
-    hipLaunchKernelGGL(k_growth_ode<false>, grid, block, 0, s, g, nodes, nsteps, table, ref);
+    hipLaunchKernelGGL(k_growth_ode<false>, grid, block, 0, s, g, sp, nodes, nsteps, table, ref);
   COLA_LAUNCH_CHECK();
 }
 
@@ -676,8 +751,7 @@ void launch_noise(const cola_params& p, int n, int pitch, int64_t plane, float* 
 
 // ------------------------------------------------------------------ delta_k -> phi1_k
 struct EHDev {
-  float A;        // sigma8 normalisation of k^ns T^2
-  float ns, th2, omh, alpha, kfac;   // kfac = 0.43 s h (s in Mpc)
+  float ns, th2, omh, alpha, kfac;   // see SpecDev
 };
 
 __device__ __forceinline__ float eh_T(const EHDev& e, float k) {
@@ -694,7 +768,7 @@ __device__ __forceinline__ float eh_T(const EHDev& e, float k) {
 __global__ void k_ic_phi1(const float2* __restrict__ wk, float2* __restrict__ phi1, int n, int pitch,
                           int64_t plane, float kf, float norm, EHDev eh,
                           const double* __restrict__ ref) {
-  const float d1 = (float)ref[0];
+  const float d1 = (float)ref[0], A = (float)ref[6];   // sigma8 normalisation of k^ns T^2
   const float inv_d1sq = 1.f / (d1 * d1);
   const int h = n / 2;
   const int64_t total = (int64_t)n * n * pitch;
@@ -711,7 +785,7 @@ __global__ void k_ic_phi1(const float2* __restrict__ wk, float2* __restrict__ ph
       const float k2 = kf * kf * (float)n2;
       const float k = sqrtf(k2);
       const float T = eh_T(eh, k);
-      const float P = eh.A * powf(k, eh.ns) * T * T * inv_d1sq;
+      const float P = A * powf(k, eh.ns) * T * T * inv_d1sq;
       const float amp = sqrtf(norm * P) / k2;
       const float2 w = wk[idx];
       out = make_float2(amp * w.x, amp * w.y);
@@ -721,19 +795,10 @@ __global__ void k_ic_phi1(const float2* __restrict__ wk, float2* __restrict__ ph
 }
 
 void launch_ic_phi1(const cola_params& p, const Layout& L, const float2* wk, float2* phi1,
-                    double A_norm, const double* ref, hipStream_t s) {
+                    const double* ref, hipStream_t s) {
   ProfScope ps("ic_phi1", s);
-  EHDev e;
-  const double omh2 = p.omega_m * p.h * p.h, obh2 = p.omega_b * p.h * p.h;
-  const double fb = p.omega_b / p.omega_m;
-  const double sh = 44.5 * std::log(9.83 / omh2) / std::sqrt(1.0 + 10.0 * std::pow(obh2, 0.75));
-  e.A = (float)A_norm;
-  e.ns = (float)p.n_s;
-  const double th = p.t_cmb / 2.7;
-  e.th2 = (float)(th * th);
-  e.omh = (float)(p.omega_m * p.h);
-  e.alpha = (float)(1.0 - 0.328 * std::log(431.0 * omh2) * fb + 0.38 * std::log(22.3 * omh2) * fb * fb);
-  e.kfac = (float)(0.43 * sh * p.h);
+  const SpecDev d = spec_dev(p);
+  const EHDev e{(float)d.ns, (float)d.th2, (float)d.omh, (float)d.alpha, (float)d.kfac};
   const double N = (double)L.N;
   const float norm = (float)(N / (p.box * p.box * p.box));
   const int64_t total = (int64_t)L.np * L.np * L.pitch_p;

@@ -144,8 +144,6 @@ struct Cosmo {
   double E(double a) const;
 };
 double tau_between(const Cosmo& c, double a0, double a1);
-double sigma8_norm(const cola_params& p);        // A with sigma8^2 = A * I
-double eh_transfer(const cola_params& p, double k);
 struct StepScalars {         // PM-force scalars at scale factor a
   double a;
   float kappa, a2m2, coupling;
@@ -288,7 +286,8 @@ void fft_autotune(const FFTPlan& pl, float2* data, hipStream_t s, int out[2]);
 
 // ------------------------------------------------------------------ kernels (launchers)
 void launch_fill(float* p, size_t n, float v, hipStream_t s);
-// growth tables (ref: the LCDM state at a = 1); scratch holds growth_scratch_bytes(p)
+// growth tables, and what the initial spectrum takes: ref[0 .. 5], the LCDM table entry at
+// a = 1, and ref[6], the sigma8 normalisation; scratch holds growth_scratch_bytes(p)
 size_t growth_scratch_bytes(const cola_params& p);
 void launch_growth_ode(const cola_params& p, const Layout& L, double* table, double* ref, void* scratch,
                        hipStream_t s);
@@ -299,7 +298,7 @@ void launch_growth_triangles(const cola_params& p, int n, const double* tri, dou
 void launch_noise(const cola_params& p, int n, int pitch, int64_t plane, float* dst_padded,
                   float* dst_flat, hipStream_t s);
 void launch_ic_phi1(const cola_params& p, const Layout& L, const float2* wk, float2* phi1,
-                    double A_norm, const double* ref, hipStream_t s);
+                    const double* ref, hipStream_t s);
 void launch_kspace(int kind, const KOp& op, float2* out, hipStream_t s);
 void launch_2lpt_diag(float* d0, const float* d1, const float* d2, size_t n, hipStream_t s);
 void launch_2lpt_sub(float* acc, const float* d, size_t n, hipStream_t s);
