@@ -204,7 +204,7 @@ static void do_prepare(const cola_params& p, cola_state* st, const Bufs& b, hipS
   COLA_HIP_CHECK(hipMemcpyAsync(b.tw_m, tm.data(), tm.size() * sizeof(float2), hipMemcpyHostToDevice, s));
   COLA_HIP_CHECK(hipMemcpyAsync(b.tw_p, tp.data(), tp.size() * sizeof(float2), hipMemcpyHostToDevice, s));
   launch_growth_ode(p, b.L, b.growth, b.ref, b.pk_scratch, s);   // the P(k) scratch is free here
-  for (int i = 0; i < p.n_steps; ++i) launch_write_step(b.steps, i, step_dev(p, b.L, i), s);
+  launch_write_steps(p, b.L, b.steps, s);
   st->prepared = 1;
 }
 
@@ -214,13 +214,14 @@ static void do_prepare(const cola_params& p, cola_state* st, const Bufs& b, hipS
 // then delta_k; mesh[2] the screening field and then S after the forward Z and Y passes;
 // the three complex force components then take slots 0-2.  If flat_out is given, rho and
 // S are copied there before being overwritten.
+// steps, ctr: where the kernels find the step's scalars (see step_entry), or null to pass
+// those of scale factor a by value.
 static void pm_core(const cola_params& p, const Bufs& b, const float* disp, double a,
-                    float* flat_out, hipStream_t s, bool from_table = false) {
+                    float* flat_out, hipStream_t s, const StepDev* steps = nullptr,
+                    const int* ctr = nullptr) {
   const Layout& L = b.L;
   const FFTPlan pl = plan_mesh(b);
   const PMScalars sc = pm_scalars(p, a);
-  const StepDev* steps = from_table ? b.steps : nullptr;
-  const int* ctr = from_table ? b.ctr : nullptr;
   float2* const* M = b.mesh;
   const float invM = (float)(1.0 / (double)L.M);
   launch_deposit(L, disp, R(M[0]), b.bins, b.entries, s);
@@ -297,9 +298,9 @@ static void pm_core(const cola_params& p, const Bufs& b, const float* disp, doub
 }
 
 // One COLA step on the given work area (st->work when null, else the library's scratch).
-// Its step-dependent scalars come from the state's step table at the device step counter,
-// which the step sets to i first (unless `replay`: a captured step that relies on the
-// counter the previous step advanced) and advances at the end.
+// Its step-dependent scalars come from entry i of the state's step table, or for `replay`,
+// a captured step that serves every step, from the entry at the device step counter, which
+// the step advances at the end.
 static void step_impl(const cola_params* p, cola_state* st, int32_t i, void* work, hipStream_t s,
                       bool replay = false) {
   if (!p) throw Error{COLA_E_ARG, "params is NULL"};
@@ -308,18 +309,19 @@ static void step_impl(const cola_params* p, cola_state* st, int32_t i, void* wor
   if (!st->prepared || st->next_step < 0) throw Error{COLA_E_STATE, "no initial conditions"};
   if (i != st->next_step) throw Error{COLA_E_STATE, "step index out of order"};
   if (i < 0 || i >= p->n_steps) throw Error{COLA_E_STATE, "step index beyond n_steps"};
-  if (!replay) launch_set_counter(b.ctr, i, s);
+  const StepDev* steps = replay ? b.steps : b.steps + i;
+  const int* ctr = replay ? b.ctr : nullptr;
   GatherArgs g{};
   g.table = b.growth;
-  g.steps = b.steps;
-  g.step_ctr = b.ctr;
-  pm_core(*p, b, st->disp, a_of_step(*p, i), nullptr, s, true);
+  g.steps = steps;
+  g.step_ctr = ctr;
+  pm_core(*p, b, st->disp, a_of_step(*p, i), nullptr, s, steps, ctr);
   if (L.kdep) {
     // L''(q, a_i) and Psi_LPT(a_{i+1}) - Psi_LPT(a_i) from the stored k-space fields,
     // after the force (their work fields and outputs may lie over mesh slots 0-2)
     const FFTPlan pp = plan_part(b);
     float2* coef = at<float2>(st->tables, L.off_lpt_coef);
-    launch_lpt_coef(L, b.growth, 0, 0, b.steps, b.ctr, coef, s);
+    launch_lpt_coef(L, b.growth, 0, 0, steps, ctr, coef, s);
     for (int t = 0; t < 2; ++t) {
       KOp op;
       op.kf = (float)(2.0 * M_PI / p->box);
@@ -337,7 +339,7 @@ static void step_impl(const cola_params* p, cola_state* st, int32_t i, void* wor
   g.disp = st->disp;
   g.vel = st->vel;
   launch_gather(L, g, s);
-  launch_step_advance(b.ctr, s);
+  if (replay) launch_step_advance(b.ctr, s);
   st->next_step = i + 1;
 }
 

@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(OpCfg<N>::T)
 k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t elemStride,
                  const float2* __restrict__ tw_g, KOp op) {
   constexpr int B = OpCfg<N>::B, E = OpCfg<N>::E, T = OpCfg<N>::T;
-  if (op.steps) op.g_n = op.steps[*op.step_ctr].sop_g_n;
+  if (op.steps) op.g_n = step_entry(op.steps, op.step_ctr).sop_g_n;
   static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
@@ -491,7 +491,7 @@ k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
                     int64_t elemStride, const float2* __restrict__ tw_g, KOp op) {
   constexpr int B = ColCfg<N>::B, E = FusedCfg<N, B>::E, T = FusedCfg<N, B>::T;
   if (op.steps) {
-    const StepDev& sd = op.steps[*op.step_ctr];
+    const StepDev& sd = step_entry(op.steps, op.step_ctr);
     op.g_n = op.step_newton ? sd.cn : sd.g_n;
     op.g_5 = op.step_newton ? 0.f : sd.g_5;
     op.a2m2 = op.step_newton ? 0.f : sd.a2m2;
@@ -1009,7 +1009,7 @@ k_fft_screen_row(float2* __restrict__ data, const float* __restrict__ rho, float
   constexpr int B = ScreenCfg<NC>::B, E = ScreenCfg<NC>::E, T = ScreenCfg<NC>::T;
   constexpr int LS = ScreenCfg<NC>::LS;
   if (sa.steps) {
-    const StepDev& sd = sa.steps[*sa.step_ctr];
+    const StepDev& sd = step_entry(sa.steps, sa.step_ctr);
     sa.thr = sd.thr;
     sa.vx = sd.vx;
     sa.vx0 = sd.vx0;

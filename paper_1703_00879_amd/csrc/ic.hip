@@ -601,8 +601,9 @@ __global__ void k_lpt_coef(const double* __restrict__ table, int64_t slice0, int
                            const StepDev* __restrict__ steps, const int* __restrict__ ctr,
                            int64_t n_k, float2* __restrict__ coef) {
   if (steps) {
-    slice0 = steps[*ctr].slice0;
-    slice1 = steps[*ctr].slice1;
+    const StepDev& sd = step_entry(steps, ctr);
+    slice0 = sd.slice0;
+    slice1 = sd.slice1;
   }
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n_k;
        k += (int64_t)gridDim.x * blockDim.x) {

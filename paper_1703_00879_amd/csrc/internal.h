@@ -175,8 +175,9 @@ struct PMScalars {
 PMScalars pm_scalars(const cola_params& p, double a);
 
 // Per-step scalars of cola_step i (a_i -> a_{i+1}), built once per run into the tables
-// buffer; the step's kernels read entry [*step counter], so one captured step can be
-// replayed for every step.  Values equal what the same step computes on the host.
+// buffer; a captured step's kernels read entry [*step counter], so that it can be replayed
+// for every step, and an uncaptured step points them at its entry.  Values equal what the
+// same step computes on the host.
 struct StepDev {
   float g_n, g_5, a2m2, sop_g_n;   // PMScalars at a_i
   float thr, vx, vx0, cn, c5;
@@ -187,6 +188,12 @@ struct StepDev {
 StepDev step_dev(const cola_params& p, const Layout& L, int i);
 // a_i, a_{i+1} and the kick and drift intervals of step i in FP64 (what step_dev rounds)
 void step_times(const cola_params& p, int i, double out[4]);
+
+// The step a step kernel runs: entry *ctr of the table while a captured step is replayed,
+// else `steps` points at the entry itself and ctr is null (no counter to set and advance).
+__device__ __forceinline__ const StepDev& step_entry(const StepDev* steps, const int* ctr) {
+  return steps[ctr ? *ctr : 0];
+}
 
 // ------------------------------------------------------------------ k-space operators
 enum KKind : int {
@@ -207,7 +214,7 @@ struct KOp {
   int64_t tab_slice0 = 0, tab_slice1 = 0;   // element offsets of two slices (K_LPT)
   int lpt_mode = 0;                // 0: X = D''(slice0); 1: X = D(slice1) - D(slice0); 2: X = D(slice0)
   const float2* coef = nullptr;    // K_LPT: the step's (X1, X2) per |nu|^2 in FP32, if built
-  // when set, the step-dependent coefficients (g_n, g_5, a2m2) come from steps[*step_ctr];
+  // when set, the step-dependent coefficients (g_n, g_5, a2m2) come from step_entry();
   // with step_newton the force pass takes the Newtonian part alone (g_n = the step's cn)
   const StepDev* steps = nullptr;
   const int* step_ctr = nullptr;
@@ -269,7 +276,7 @@ void fft_c2r_lpt3(const FFTPlan& pl, const KOp& op, const float2* phi1, const fl
 // s_out (optional, padded real) receives S = delta eps.
 struct ScreenArgs {
   float thr, vx, vx0, cn, c5;      // see PMScalars
-  const StepDev* steps = nullptr;  // when set, the five come from steps[*step_ctr]
+  const StepDev* steps = nullptr;  // when set, the five come from step_entry()
   const int* step_ctr = nullptr;
 };
 void fft_screen(const FFTPlan& pl, int kind, const KOp& op, float2* dk, float2* data,
@@ -312,14 +319,14 @@ void launch_combine_u0(const Layout& L, const float* psi1, const float* psi2,
 // D2(a_i)) (differences taken in FP64), from table slices at element offsets slice0/slice1.
 void launch_lpt_coef(const Layout& L, const double* table, int64_t slice0, int64_t slice1,
                      const StepDev* steps, const int* ctr, float2* coef, hipStream_t s);
-// step table and counter: steps[i] = v; *ctr = v; *ctr += 1 (single-thread kernels)
-void launch_write_step(StepDev* steps, int i, const StepDev& v, hipStream_t s);
+// the step table of a run; the step counter: *ctr = v; *ctr += 1 (single-thread kernels)
+void launch_write_steps(const cola_params& p, const Layout& L, StepDev* steps, hipStream_t s);
 void launch_set_counter(int* ctr, int v, hipStream_t s);
 void launch_step_advance(int* ctr, hipStream_t s);
 // k-Mouflage source (App. B): out = (rho - 1)(cn + c5 eps) in the padded real layout, with
 // eps = min(1, 1/P_X(X*)), P_X(X*)^2 X* = km_r |F|^2 from the interleaved Newtonian force
 // mesh f3; s_out (optional, padded real) gets S = (rho - 1) eps.  With steps set, km_r, cn
-// and c5 come from steps[*step_ctr].
+// and c5 come from step_entry().
 struct KmArgs {
   float km_r, k0, cn, c5;
   int m;
@@ -345,7 +352,7 @@ struct GatherArgs {
   int64_t slice0, slice1;     // element offsets of slices i and i+1
   double dtk, dtd;
   float* force_out;           // cola_pm_force: write F_p instead of updating
-  const StepDev* steps;       // when set, dtk, dtd, slice0, slice1 come from steps[*step_ctr]
+  const StepDev* steps;       // when set, dtk, dtd, slice0, slice1 come from step_entry()
   const int* step_ctr;
 };
 void launch_gather(const Layout& L, const GatherArgs& g, hipStream_t s);

@@ -535,7 +535,7 @@ template <int MODE>
 __global__ void __launch_bounds__(256)
 k_gather(GatherDev g, int64_t N, int np, int nm, int ratio, float inv_cell, int bricks) {
   if (MODE != 2 && g.steps) {
-    const StepDev& sd = g.steps[*g.step_ctr];
+    const StepDev& sd = step_entry(g.steps, g.step_ctr);
     g.dtk = sd.dtk;
     g.dtd = sd.dtd;
     g.slice0 = sd.slice0;
@@ -678,7 +678,7 @@ __global__ void k_kmouflage_source(const float* __restrict__ rho, const float* _
                                    float* __restrict__ out, float* __restrict__ s_out, int n,
                                    int rpitch, int64_t rplane, KmArgs k) {
   if (k.steps) {
-    const StepDev& sd = k.steps[*k.step_ctr];
+    const StepDev& sd = step_entry(k.steps, k.step_ctr);
     k.km_r = sd.km_r;
     k.cn = sd.cn;
     k.c5 = sd.c5;
@@ -706,13 +706,26 @@ void launch_kmouflage_source(const Layout& L, const float* rho, const float* f3,
 }
 
 // ------------------------------------------------------------------ step table and counter
-__global__ void k_write_step(StepDev* steps, int i, StepDev v) { steps[i] = v; }
+// Entries of the step table, kStepsPerLaunch at a time by value (2.3 KB of kernel arguments):
+// one launch for a run of up to 32 steps where one launch an entry took 4.5 us each.
+constexpr int kStepsPerLaunch = 32;
+struct StepBatch {
+  StepDev v[kStepsPerLaunch];
+};
+__global__ void k_write_steps(StepDev* steps, int n, StepBatch b) {
+  if ((int)threadIdx.x < n) steps[threadIdx.x] = b.v[threadIdx.x];
+}
 __global__ void k_set_counter(int* ctr, int v) { *ctr = v; }
 __global__ void k_step_advance(int* ctr) { *ctr += 1; }
 
-void launch_write_step(StepDev* steps, int i, const StepDev& v, hipStream_t s) {
-  hipLaunchKernelGGL(k_write_step, dim3(1), dim3(1), 0, s, steps, i, v);
-  COLA_LAUNCH_CHECK();
+void launch_write_steps(const cola_params& p, const Layout& L, StepDev* steps, hipStream_t s) {
+  for (int i0 = 0; i0 < p.n_steps; i0 += kStepsPerLaunch) {
+    const int n = std::min(kStepsPerLaunch, p.n_steps - i0);
+    StepBatch b;
+    for (int i = 0; i < n; ++i) b.v[i] = step_dev(p, L, i0 + i);
+    hipLaunchKernelGGL(k_write_steps, dim3(1), dim3(kStepsPerLaunch), 0, s, steps + i0, n, b);
+    COLA_LAUNCH_CHECK();
+  }
 }
 void launch_set_counter(int* ctr, int v, hipStream_t s) {
   hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, ctr, v);
