@@ -107,7 +107,6 @@ struct Bufs {
   float2* tw_p;
   void* pk_scratch;
   float4* pk_out;
-  unsigned long long* pk_cnt;
   float2* mesh[6];
   float* force;       // interleaved force mesh over slots 3-5
   float2* lptw[3];    // scale-dependent LPT: particle-grid work fields
@@ -155,7 +154,6 @@ static Bufs carve(const cola_params& p, const cola_state* st, void* work = nullp
   b.tw_p = at<float2>(st->tables, L.off_tw_p);
   b.pk_scratch = at<void>(st->tables, L.off_scratch);
   b.pk_out = at<float4>(st->tables, L.off_scratch + pk_scratch_bytes(L, 2048));
-  b.pk_cnt = reinterpret_cast<unsigned long long*>(b.pk_out + 2048);
   b.steps = at<StepDev>(st->tables, L.off_steps);
   b.ctr = at<int>(st->tables, L.off_ctr);
   for (int i = 0; i < 6; ++i) b.mesh[i] = at<float2>(work, L.off_mesh[i]);
@@ -645,14 +643,18 @@ cola_status cola_power_spectrum(const cola_params* p, cola_state* st, int32_t nb
     if (!st->prepared) throw Error{COLA_E_STATE, "state not prepared"};
     if (nbins < 1 || nbins > 2048) throw Error{COLA_E_ARG, "nbins must be in [1, 2048]"};
     launch_deposit(b.L, st->disp, R(b.mesh[0]), b.bins, b.entries, s);
-    fft_r2c(plan_mesh(b), R(b.mesh[0]), b.mesh[1], s);
-    launch_pk(b.L, b.mesh[1], nbins, b.pk_scratch, b.pk_out, b.pk_cnt, s);
+    fft_r2c_zy(plan_mesh(b), R(b.mesh[0]), b.mesh[1], s);   // the X pass bins the modes
+    // the sums and the counts lie side by side, so that one copy brings both
+    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(b.pk_out + nbins);
+    launch_pk(b.L, plan_mesh(b), b.mesh[1], nbins, b.pk_scratch, b.pk_out, cnt, s);
+    const size_t row = sizeof(float4) + sizeof(unsigned long long);
+    std::vector<unsigned char> host(nbins * row);
+    COLA_HIP_CHECK(hipMemcpyAsync(host.data(), b.pk_out, nbins * row, hipMemcpyDeviceToHost, s));
+    COLA_HIP_CHECK(hipStreamSynchronize(s));
     std::vector<float4> o(nbins);
     std::vector<unsigned long long> c(nbins);
-    COLA_HIP_CHECK(hipMemcpyAsync(o.data(), b.pk_out, nbins * sizeof(float4), hipMemcpyDeviceToHost, s));
-    COLA_HIP_CHECK(hipMemcpyAsync(c.data(), b.pk_cnt, nbins * sizeof(unsigned long long),
-                                  hipMemcpyDeviceToHost, s));
-    COLA_HIP_CHECK(hipStreamSynchronize(s));
+    std::memcpy(o.data(), host.data(), nbins * sizeof(float4));
+    std::memcpy(c.data(), host.data() + nbins * sizeof(float4), nbins * sizeof(unsigned long long));
     for (int i = 0; i < nbins; ++i) {
       const double w = (double)c[i];
       const double sp = (double)o[i].x + (double)o[i].y;

@@ -282,6 +282,20 @@ struct ScreenArgs {
 void fft_screen(const FFTPlan& pl, int kind, const KOp& op, float2* dk, float2* data,
                 const float* rho, float* s_out, int model, const ScreenArgs& sa, hipStream_t s);
 
+// Forward X pass of `data` (Z and Y passes done) that bins the modes' power instead of
+// writing them: part[block * nbins + b] gets each block's sum of w P over shell b, P =
+// vol |delta_k|^2 / W^2 formed in FP32 per mode (W the CIC window from wtab[|nu|] per axis,
+// delta_k unnormalised / n^3) and summed in FP64.  Returns the number of blocks, at most
+// kPkBlocks.
+constexpr int kPkBlocks = 1024;
+struct PkBin {
+  int pitch, nbins;
+  float vol;
+  const float* wtab;
+  double* part;
+};
+int fft_x_pk(const FFTPlan& pl, const float2* data, const PkBin& a, hipStream_t s);
+
 // Tile widths (columns per work-group) of the Y passes of n-point transforms, per
 // direction: fwd / inv = 4, 8 or 16 sets one (COLA_E_ARG if it does not fit LDS or the
 // work-group limit at n), 0 restores the default, -1 leaves it.  fft_get_tiles gives the
@@ -363,10 +377,11 @@ void launch_unpad_mesh(const Layout& L, const float* padded, float* flat, hipStr
                        float sub = 0.f);
 void launch_positions(const cola_params& p, const Layout& L, const float* disp, float* xyz,
                       hipStream_t s);
-// P(k) shell sums with per-block partials and a compensated cross-block reduction.
-// Writes out[b] = (sum w P hi, lo, sum w |k| hi, lo) and counts[b] = sum w (device).
+// P(k) shell sums of the field `dk` after its forward Z and Y passes, with per-block partials
+// and a compensated cross-block reduction.  Writes out[b] = (sum w P hi, lo, sum w |k| hi, lo)
+// and counts[b] = sum w (device).
 size_t pk_scratch_bytes(const Layout& L, int nbins);
-void launch_pk(const Layout& L, const float2* dk, int nbins, void* scratch, float4* out,
+void launch_pk(const Layout& L, const FFTPlan& pl, const float2* dk, int nbins, void* scratch, float4* out,
                unsigned long long* counts, hipStream_t s);
 
 }  // namespace cola

@@ -141,4 +141,16 @@ __device__ __forceinline__ float2 grad_minus_i(const KOp& op, int ix, int iy, in
   return make_float2(k * g.y, -k * g.x);
 }
 
+// P(k) shells.
+// Bin b = floor(|nu| + 1/2) from the integer |nu|^2: b^2 - b < n2 <= b^2 + b.  The integer
+// tests correct a root that is an ulp off, so the hardware root gives the same bins as an
+// exact one; every product is below 2^24.
+__device__ __forceinline__ int shell_of(int n2) {
+  int b = (int)(fast_sqrt((float)n2) + 0.5f);
+  const int t = __mul24(b, b);
+  if (b > 0 && t - b >= n2) --b;
+  else if (n2 > t + b) ++b;
+  return b;
+}
+
 }  // namespace cola

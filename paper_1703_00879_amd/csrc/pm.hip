@@ -900,115 +900,137 @@ void launch_positions(const cola_params& p, const Layout& L, const float* disp, 
 }
 
 // ------------------------------------------------------------------ power spectrum
-// Bin b = floor(|nu| + 1/2) from the integer |nu|^2: b^2 - b < n2 <= b^2 + b.
-__device__ __forceinline__ int shell_of(int n2) {
-  int b = (int)floorf(sqrtf((float)n2) + 0.5f);
-  if (b > 0 && b * b - b >= n2) --b;
-  if (n2 > b * b + b) ++b;
-  return b;
-}
-
 __device__ __forceinline__ float sincf_pi(float x) {   // sin(pi x)/(pi x)
   return x == 0.f ? 1.f : sinpif(x) / (3.14159265358979323846f * x);
 }
 
-constexpr int kPkBlocks = 1024;
 constexpr int kPkMaxBins = 2048;
+constexpr int kPkModeBlocks = 512;
 
-// Per block: LDS shell sums of w, w P and w |k| over a grid-stride share of the modes.
-// Each mode's terms are formed in FP32 and summed in FP64 (LDS double atomics), so the
-// order in which a block's threads add them changes only the last bits of a 53-bit sum.
+// What the shells hold apart from the field: the mode counts and the sums of |k|, and the
+// CIC window per axis, wtab[|nu|] = sinc(nu / n).  Both sums depend on |nu_x|, |nu_y| and
+// nu_z alone, so one wave takes a row of nu_z for each unordered pair (|nu_x|, |nu_y|) with its
+// multiplicity, an eighth of the modes, instead of two LDS atomics for every mode of the
+// field (a mode's |k| term is formed in FP32 and summed in FP64, exactly as if each mode
+// added its own).  Bound by its LDS atomics: 146 us at n = 1024.
 __global__ void __launch_bounds__(256)
-k_pk_partial(const float2* __restrict__ dk, int n, int pitch, int64_t plane, int nbins, float kf,
-             float vol,
-             double* __restrict__ part_p, double* __restrict__ part_k,
-             unsigned* __restrict__ part_w) {
-  __shared__ double sp[kPkMaxBins], sk[kPkMaxBins];
+k_pk_modes(int n, int nbins, float kf, float* __restrict__ wtab, double* __restrict__ part_k,
+           unsigned* __restrict__ part_w) {
+  __shared__ double sk[kPkMaxBins];
   __shared__ unsigned sw[kPkMaxBins];
   for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-    sp[b] = 0.0;
     sk[b] = 0.0;
     sw[b] = 0u;
   }
   __syncthreads();
   const int h = n / 2;
-  const int64_t total = (int64_t)n * n * (h + 1);
-  const float invM = 1.f / ((float)n * (float)n * (float)n);
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int iz = (int)(e % (h + 1));
-    const int64_t r = e / (h + 1);
-    const int iy = (int)(r % n), ix = (int)(r / n);
-    const int nx = ix < h ? ix : ix - n, ny = iy < h ? iy : iy - n;
-    const int n2 = nx * nx + ny * ny + iz * iz;
-    if (n2 == 0) continue;
-    const int b = shell_of(n2);
-    if (b >= nbins) continue;
-    const float2 v = dk[ix * plane + (int64_t)iy * pitch + iz];
-    const float wx = sincf_pi((float)nx / n), wy = sincf_pi((float)ny / n),
-                wz = sincf_pi((float)iz / n);
-    const float W = wx * wx * wy * wy * wz * wz;
-    const float ar = v.x * invM / W, ai = v.y * invM / W;
-    const unsigned w = (iz > 0 && iz < h) ? 2u : 1u;
-    atomicAdd(&sp[b], (double)((float)w * vol * (ar * ar + ai * ai)));
-    atomicAdd(&sk[b], (double)((float)w * kf * sqrtf((float)n2)));
-    atomicAdd(&sw[b], w);
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i <= h; i += blockDim.x) wtab[i] = sincf_pi((float)i / n);
+  const int rows = (h + 1) * (h + 2) / 2, waves = gridDim.x * (blockDim.x >> 6);
+  for (int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); r < rows; r += waves) {
+    int a = (int)((sqrtf(8.f * (float)r + 1.f) - 1.f) * 0.5f);   // row r = a (a + 1)/2 + b, b <= a
+    while (a * (a + 1) / 2 > r) --a;
+    while ((a + 1) * (a + 2) / 2 <= r) ++a;
+    const int b = r - a * (a + 1) / 2;
+    const unsigned mult = (a == 0 || a == h ? 1u : 2u) * (b == 0 || b == h ? 1u : 2u) * (a != b ? 2u : 1u);
+    for (int iz = threadIdx.x & 63; iz <= h; iz += 64) {
+      const int n2 = a * a + b * b + iz * iz;
+      const int bin = shell_of(n2);
+      if (n2 == 0 || bin >= nbins) continue;
+      const unsigned w = (iz > 0 && iz < h) ? 2u : 1u;
+      atomicAdd(&sk[bin], (double)mult * (double)((float)w * kf * sqrtf((float)n2)));
+      atomicAdd(&sw[bin], mult * w);
+    }
   }
   __syncthreads();
   for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-    part_p[(int64_t)blockIdx.x * nbins + b] = sp[b];
     part_k[(int64_t)blockIdx.x * nbins + b] = sk[b];
     part_w[(int64_t)blockIdx.x * nbins + b] = sw[b];
   }
 }
 
-// Cross-block reduction per bin in FP64, block after block (a fixed order), with
-// Neumaier compensation; each sum leaves as an FP32 pair hi + lo.
-__global__ void k_pk_final(const double* __restrict__ part_p, const double* __restrict__ part_k,
-                           const unsigned* __restrict__ part_w, int nblk, int nbins,
-                           float4* __restrict__ out, unsigned long long* __restrict__ counts) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nbins) return;
-  double sp = 0.0, cp = 0.0, sk = 0.0, ck = 0.0;
+// Cross-block reduction per bin in FP64: kPkSeg threads share a bin, each adding every
+// kPkSeg-th block with Neumaier compensation, and the first adds their sums in order (a
+// fixed order for a given grid); each sum leaves as an FP32 pair hi + lo.  One thread a bin
+// walking all blocks took 316 us (512 bins, 1024 blocks: 425 us), this takes 12.
+constexpr int kPkSeg = 32;
+__global__ void __launch_bounds__(8 * kPkSeg)
+k_pk_final(const double* __restrict__ part_p, int nblk_p, const double* __restrict__ part_k,
+           const unsigned* __restrict__ part_w, int nblk_k, int nbins, float4* __restrict__ out,
+           unsigned long long* __restrict__ counts) {
+  __shared__ double rs[2][kPkSeg][8], rc[2][kPkSeg][8];
+  __shared__ unsigned long long rw[kPkSeg][8];
+  const int lb = threadIdx.x & 7, seg = threadIdx.x >> 3, b = blockIdx.x * 8 + lb;
+  auto add = [](double& s, double& c, double x) {
+    const double t = s + x;
+    c += (fabs(s) >= fabs(x)) ? (s - t) + x : (x - t) + s;
+    s = t;
+  };
+  auto sum = [&](const double* part, int nblk, int which) {
+    double s = 0.0, c = 0.0;
+    if (b < nbins)
+#pragma unroll 8
+      for (int i = seg; i < nblk; i += kPkSeg) add(s, c, part[(int64_t)i * nbins + b]);
+    rs[which][seg][lb] = s;
+    rc[which][seg][lb] = c;
+  };
+  sum(part_p, nblk_p, 0);
+  sum(part_k, nblk_k, 1);
   unsigned long long w = 0;
-  for (int i = 0; i < nblk; ++i) {
-    const double xp = part_p[(int64_t)i * nbins + b];
-    double t = sp + xp;
-    cp += (fabs(sp) >= fabs(xp)) ? (sp - t) + xp : (xp - t) + sp;
-    sp = t;
-    const double xk = part_k[(int64_t)i * nbins + b];
-    t = sk + xk;
-    ck += (fabs(sk) >= fabs(xk)) ? (sk - t) + xk : (xk - t) + sk;
-    sk = t;
-    w += part_w[(int64_t)i * nbins + b];
+  if (b < nbins)
+#pragma unroll 8
+    for (int i = seg; i < nblk_k; i += kPkSeg) w += part_w[(int64_t)i * nbins + b];
+  rw[seg][lb] = w;
+  __syncthreads();
+  if (seg != 0 || b >= nbins) return;
+  double v[2];
+  for (int q = 0; q < 2; ++q) {
+    double s = 0.0, c = 0.0;
+    for (int i = 0; i < kPkSeg; ++i) {
+      add(s, c, rs[q][i][lb]);
+      c += rc[q][i][lb];
+    }
+    v[q] = s + c;
   }
-  const double P = sp + cp, K = sk + ck;
-  const float ph = (float)P, kh = (float)K;
-  out[b] = make_float4(ph, (float)(P - (double)ph), kh, (float)(K - (double)kh));
+  for (int i = 1; i < kPkSeg; ++i) w += rw[i][lb];
+  const float ph = (float)v[0], kh = (float)v[1];
+  out[b] = make_float4(ph, (float)(v[0] - (double)ph), kh, (float)(v[1] - (double)kh));
   counts[b] = w;
 }
 
-size_t pk_scratch_bytes(const Layout&, int nbins) {
-  return align_up((size_t)kPkBlocks * nbins * (2 * sizeof(double) + sizeof(unsigned)));
+// scratch: the field's partial sums (at most kPkBlocks rows of nbins), then the modes' (|k|,
+// then counts) and the window table
+size_t pk_scratch_bytes(const Layout& L, int nbins) {
+  return align_up((size_t)nbins * (kPkBlocks * sizeof(double) + kPkModeBlocks * (sizeof(double) + sizeof(unsigned))) +
+                  (size_t)(L.nm / 2 + 1) * sizeof(float));
 }
 
-void launch_pk(const Layout& L, const float2* dk, int nbins, void* scratch, float4* out,
+void launch_pk(const Layout& L, const FFTPlan& pl, const float2* dk, int nbins, void* scratch, float4* out,
                unsigned long long* counts, hipStream_t s) {
   if (nbins > kPkMaxBins) throw Error{COLA_E_ARG, "nbins exceeds 2048"};
   double* part_p = static_cast<double*>(scratch);
   double* part_k = part_p + (size_t)kPkBlocks * nbins;
-  unsigned* part_w = reinterpret_cast<unsigned*>(part_k + (size_t)kPkBlocks * nbins);
+  unsigned* part_w = reinterpret_cast<unsigned*>(part_k + (size_t)kPkModeBlocks * nbins);
+  float* wtab = reinterpret_cast<float*>(part_w + (size_t)kPkModeBlocks * nbins);
   const float kf = (float)(2.0 * M_PI / L.box);
-  const float vol = (float)(L.box * L.box * L.box);
+  const int h = L.nm / 2, rows = (h + 1) * (h + 2) / 2;
+  const int mode_blocks = std::min(kPkModeBlocks, (rows + 7) / 8);   // two rows a wave or more
   {
-    ProfScope ps("pk_bin", s);
-    hipLaunchKernelGGL(k_pk_partial, dim3(kPkBlocks), dim3(256), 0, s, dk, L.nm, L.pitch_m, L.plane_m, nbins,
-                       kf, vol, part_p, part_k, part_w);
+    ProfScope ps("pk_modes", s);
+    hipLaunchKernelGGL(k_pk_modes, dim3(mode_blocks), dim3(256), 0, s, L.nm, nbins, kf, wtab, part_k,
+                       part_w);
     COLA_LAUNCH_CHECK();
   }
+  PkBin a;
+  a.pitch = L.pitch_m;
+  a.nbins = nbins;
+  a.vol = (float)(L.box * L.box * L.box);
+  a.wtab = wtab;
+  a.part = part_p;
+  const int nblk = fft_x_pk(pl, dk, a, s);
   ProfScope ps("pk_final", s);
-  hipLaunchKernelGGL(k_pk_final, dim3((nbins + 63) / 64), dim3(64), 0, s, part_p, part_k, part_w,
-                     kPkBlocks, nbins, out, counts);
+  hipLaunchKernelGGL(k_pk_final, dim3((nbins + 7) / 8), dim3(8 * kPkSeg), 0, s, part_p, nblk, part_k, part_w,
+                     mode_blocks, nbins, out, counts);
   COLA_LAUNCH_CHECK();
 }
 
