@@ -267,6 +267,7 @@ _SYMBOLS = [("k_fft_col_fwd_force<{n}, true>", "fft_x_fwd_force"),
             ("k_fft_c2r_row<{nph}>", "lpt_fft_c2r_z"),
             ("k_fft_screen_row", "fft_z_screen"), ("k_fft_r2c_row", "fft_r2c_z"),
             ("k_gather", "gather_kick_drift"), ("k_deposit_tiles", "deposit"), ("k_bin<0,", "bin_count"),
+            ("k_bin_count", "bin_count"), ("k_bin_scatter", "bin_scatter"),
             ("k_bin<1,", "bin_scatter"), ("k_scan_", "bin_scan"), ("k_fill", "fill")]
 
 

@@ -222,7 +222,7 @@ static void pm_core(const cola_params& p, const Bufs& b, const float* disp, doub
   const PMScalars sc = pm_scalars(p, a);
   float2* const* M = b.mesh;
   const float invM = (float)(1.0 / (double)L.M);
-  launch_deposit(L, disp, R(M[0]), b.bins, b.entries, s);
+  launch_deposit(L, disp, R(M[0]), b.bins, b.entries, M[1], s);
   if (flat_out) launch_unpad_mesh(L, R(M[0]), flat_out, s);
   fft_r2c_zy(pl, R(M[0]), M[1], s);   // the X pass is fused into what follows
   const float2* dk = nullptr;
@@ -246,7 +246,7 @@ static void pm_core(const cola_params& p, const Bufs& b, const float* disp, doub
     nop.step_newton = 1;
     float2* const w0[3] = {M[0], M[1], M[2]};
     fft_c2r_force3(pl, nop, nullptr, M[1], w0, b.force, s);
-    launch_deposit(L, disp, R(M[0]), b.bins, b.entries, s);
+    launch_deposit(L, disp, R(M[0]), b.bins, b.entries, M[1], s);
     KmArgs ka;
     ka.km_r = sc.km_r;
     ka.k0 = (float)p.km_k0;
@@ -642,7 +642,7 @@ cola_status cola_power_spectrum(const cola_params* p, cola_state* st, int32_t nb
     const Bufs b = carve(*p, st);
     if (!st->prepared) throw Error{COLA_E_STATE, "state not prepared"};
     if (nbins < 1 || nbins > 2048) throw Error{COLA_E_ARG, "nbins must be in [1, 2048]"};
-    launch_deposit(b.L, st->disp, R(b.mesh[0]), b.bins, b.entries, s);
+    launch_deposit(b.L, st->disp, R(b.mesh[0]), b.bins, b.entries, b.mesh[1], s);
     fft_r2c_zy(plan_mesh(b), R(b.mesh[0]), b.mesh[1], s);   // the X pass bins the modes
     // the sums and the counts lie side by side, so that one copy brings both
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(b.pk_out + nbins);

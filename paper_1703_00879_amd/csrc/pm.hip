@@ -65,17 +65,21 @@ void launch_fill(float* p, size_t n, float v, hipStream_t s) {
 // run far below HBM bandwidth, so the deposit is a counting sort instead:
 //  1. count: every particle finds its home tile (the T^3-cell tile holding its lower CIC
 //     corner i0) and its class c = bitmask of the axes on which i0 sits on the tile's
-//     last layer (c != 0: some corners spill into the next tile).  Work-groups take
-//     Lagrangian bricks of 4x8x8 particles, which land in few tiles; the lanes of a wave
-//     that share a (tile, class) make one global add between them;
-//  2. scan: exclusive prefix over tiles, then per-class cursors inside each tile;
-//  3. scatter: the same bricks write CIC records into the tile/class segments;
+//     last layer (c != 0: some corners spill into the next tile), and its rank among the
+//     particles of the same (tile, class).  Work-groups take Lagrangian bricks of 4x8x8
+//     particles, which land in few tiles, and count in LDS before they add to the
+//     global counters;
+//  2. scan: exclusive prefix over tiles, then the first place of each class in its tile;
+//  3. scatter: every particle writes its CIC record to its class's first place plus its rank
+//     (4 bytes a particle written by the count and read here, instead of a second round of
+//     returning atomics);
 //  4. deposit: one work-group per tile accumulates in LDS the corners that fall inside it
 //     -- from every particle of its own tile and from the class-c particles of the seven
 //     lower neighbour tiles T - delta with (c & delta) == delta -- and writes the tile
 //     once with plain stores, so the mesh needs no zeroing pass.
 constexpr int kBrickX = 4, kBrickY = 8, kBrickZ = 8;   // 256 particles per brick
-constexpr int kBinBricks = 2;                           // bricks per binning work-group
+constexpr int kBinBricks = 2;                           // bricks a counting work-group takes at a time
+constexpr int kScatterBricks = 2;                       // bricks per scatter work-group
 constexpr int kScanBlock = 1024;                        // tiles per scan block
 constexpr float kFix = 16777216.f;                      // 2^24: deposit fixed-point unit
 // Threads per tile work-group: the LDS accumulator (32 KB for 16^3 cells) allows four
@@ -150,92 +154,180 @@ __device__ __forceinline__ float rec_d(uint32_t v) {
   return (float)(v & 0x0FFFFFFFu) * (1.f / 268435456.f);
 }
 
-// MODE 0: count into cnt[tile*8 + cls];  MODE 1: scatter the particle's CIC record
-// (offsets and lower corner relative to its home tile) to entries[cur[tile*8 + cls]++].
-// A work-group takes kBinBricks consecutive bricks and each thread one particle of each,
-// with all displacement loads issued up front.  The lanes of a wave that share a
-// (tile, class) key are served by one atomic that adds their number; in MODE 1 each lane
-// takes the returned base plus its rank among them.  A wave holds an 8 x 8 patch of one
-// lattice plane, so it meets only a few keys.
-template <int MODE, bool P2>
+// A particle's sort key, tile * 8 + class, and its CIC record.
+template <bool P2>
+__device__ __forceinline__ unsigned bin_key(const BinGeo& g, int ix, int iy, int iz, float ux, float uy,
+                                            float uz, CicRec& rec) {
+  float dx, dy, dz;
+  const int cx = axis_cell<P2>(ix, ux, g, dx);
+  const int cy = axis_cell<P2>(iy, uy, g, dy);
+  const int cz = axis_cell<P2>(iz, uz, g, dz);
+  const int lt = g.lt, m = g.tile - 1;
+  const int tile = ((cx >> lt) * g.nt1 + (cy >> lt)) * g.nt1 + (cz >> lt);
+  const int cls = ((cx & m) == m ? 1 : 0) | ((cy & m) == m ? 2 : 0) | ((cz & m) == m ? 4 : 0);
+  rec = CicRec{rec_axis(cx & m, dx), rec_axis(cy & m, dy), rec_axis(cz & m, dz)};
+  return (unsigned)tile * 8u + (unsigned)cls;
+}
+
+// Count: cnt[key] += the particles of each key, and rank[] gets every particle's place among
+// its key's (in brick order: rank[brick * 256 + thread]).
+//
+// A work-group takes `iters` pairs of consecutive bricks, each thread one particle of each
+// brick, and counts in an LDS hash table first: the lanes of a wave that share a key are
+// grouped by ballots (a wave holds an 8 x 8 patch of one lattice plane, so it meets few
+// keys), each group makes one LDS add, and each key of the table makes one global add at
+// the end.  What bounds the pass otherwise, once many particles from all over the box sit in
+// few cells, is the rate of global adds to one cache line of counters, one in 11 ns: 512^3
+// particles, a quarter of them in 64 clumps, were counted in 6.3 ms with one global add a
+// group and scattered in another 6.3; now 2.0 and 1.55 (unclustered 0.52 + 0.96, now 0.67 +
+// 1.0: the rank costs 8 bytes a particle).  A key that finds no slot within kBinProbe goes to
+// the global counter directly.
+constexpr int kBinIters = 8;        // at most; large runs take all, small ones fill the chip
+constexpr int kBinHash = 1024;      // slots: 16 bricks late in a run meet a few hundred keys
+constexpr int kBinProbe = 16;
+constexpr int kBinGroups = 12;
+constexpr uint32_t kBinEmpty = 0xffffffffu, kBinDirect = 0x80000000u;
+
+template <bool P2>
 __global__ void __launch_bounds__(256)
-k_bin(const float* __restrict__ disp, BinGeo g, uint32_t* __restrict__ cnt,
-      uint32_t* __restrict__ cur, CicRec* __restrict__ entries) {
+k_bin_count(const float* __restrict__ disp, BinGeo g, int iters, uint32_t* __restrict__ cnt,
+            uint32_t* __restrict__ rank, int nbricks) {
   constexpr int S = kBinBricks;
-  const int b0 = (int)xcd_block(blockIdx.x, gridDim.x) * S;
-  bool valid[S];
-  int64_t p[S];
-  int ix[S], iy[S], iz[S];
-  float ux[S], uy[S], uz[S];
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    p[s] = 0;
-    ix[s] = iy[s] = iz[s] = 0;
-    valid[s] = brick_particle<P2>(g, b0 + s, ix[s], iy[s], iz[s], p[s]);
-    ux[s] = uy[s] = uz[s] = 0.f;
-    if (valid[s]) {
-      ux[s] = disp[p[s]];
-      uy[s] = disp[g.N + p[s]];
-      uz[s] = disp[2 * g.N + p[s]];
-    }
+  __shared__ uint32_t hkey[kBinHash], hcnt[kBinHash];
+  // a particle's (slot << 16 | rank within the work-group), or kBinDirect | its final rank
+  __shared__ uint32_t code[kBinIters * S * 256];
+  for (int i = threadIdx.x; i < kBinHash; i += 256) {
+    hkey[i] = kBinEmpty;
+    hcnt[i] = 0u;
   }
+  __syncthreads();
+  const int first = (int)xcd_block(blockIdx.x, gridDim.x) * S * iters;
   const int lane = (int)__lane_id();
-  uint32_t gbase[S], myrank[S];
-  int mygroup[S];
-  CicRec rec[S];
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    unsigned key = 0xffffffffu;
-    rec[s] = CicRec{0u, 0u, 0u};
-    if (valid[s]) {
-      float dx, dy, dz;
-      const int cx = axis_cell<P2>(ix[s], ux[s], g, dx);
-      const int cy = axis_cell<P2>(iy[s], uy[s], g, dy);
-      const int cz = axis_cell<P2>(iz[s], uz[s], g, dz);
-      const int lt = g.lt, m = g.tile - 1;
-      const int tile = ((cx >> lt) * g.nt1 + (cy >> lt)) * g.nt1 + (cz >> lt);
-      const int cls = ((cx & m) == m ? 1 : 0) | ((cy & m) == m ? 2 : 0) | ((cz & m) == m ? 4 : 0);
-      rec[s] = CicRec{rec_axis(cx & m, dx), rec_axis(cy & m, dy), rec_axis(cz & m, dz)};
-      key = (unsigned)tile * 8u + (unsigned)cls;
-    }
-    // group the wave's lanes by key with ballots (no memory traffic); group i's key and
-    // size land in lane i, which then makes the group's one atomic -- all groups' atomics
-    // go out as a single wave instruction
-    unsigned long long todo = __ballot(valid[s]);
-    int it = 0;
-    uint32_t gcnt = 0;
-    unsigned gkey = 0;
-    mygroup[s] = 0;
-    myrank[s] = 0;
-    while (todo) {   // wave-uniform: every lane runs the same iterations, at most 64
-      const int leader = __ffsll((unsigned long long)todo) - 1;
-      const unsigned lkey = __shfl(key, leader);
-      const unsigned long long m = __ballot(key == lkey) & todo;
-      if (lane == it) {
-        gkey = lkey;
-        gcnt = (uint32_t)__popcll(m);
-      }
-      if ((m >> lane) & 1ull) {
-        mygroup[s] = it;
-        myrank[s] = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-      }
-      todo &= ~m;
-      ++it;
-    }
-    gbase[s] = 0;
-    if (lane < it) {
-      if (MODE == 0)
-        atomicAdd(&cnt[gkey], gcnt);
-      else
-        gbase[s] = atomicAdd(&cur[gkey], gcnt);
-    }
-  }
-  if (MODE == 1) {
+  struct Next {   // the particles of the coming pair of bricks, loaded ahead
+    bool valid;
+    int ix, iy, iz;
+    float ux, uy, uz;
+  } nx[S];
+  auto issue = [&](int it) {
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const uint32_t base = __shfl(gbase[s], mygroup[s]);
-      if (valid[s]) entries[base + myrank[s]] = rec[s];
+      int64_t p = 0;
+      nx[s] = Next{false, 0, 0, 0, 0.f, 0.f, 0.f};
+      if (it < iters) nx[s].valid = brick_particle<P2>(g, first + it * S + s, nx[s].ix, nx[s].iy, nx[s].iz, p);
+      if (nx[s].valid) {
+        nx[s].ux = disp[p];
+        nx[s].uy = disp[g.N + p];
+        nx[s].uz = disp[2 * g.N + p];
+      }
     }
+  };
+  issue(0);
+  for (int it = 0; it < iters; ++it) {
+    unsigned kk[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      CicRec rec;
+      kk[s] = nx[s].valid ? bin_key<P2>(g, nx[s].ix, nx[s].iy, nx[s].iz, nx[s].ux, nx[s].uy, nx[s].uz, rec)
+                          : kBinEmpty;
+    }
+    issue(it + 1);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const unsigned key = kk[s];
+      // Group the wave's lanes by key; group i's key and size go to lane i, which makes the
+      // group's one add -- all groups' adds go out as a single wave instruction.  The loop is
+      // wave-uniform (scalar mask, leader and key: a dozen instructions a group).  After
+      // kBinGroups groups the lanes left, whose keys are then nearly all different, add
+      // for themselves.
+      unsigned long long todo = __ballot(key != kBinEmpty);
+      int ng = 0, mygroup = 0;
+      uint32_t gcnt = 0, myrank = 0;
+      unsigned gkey = 0;
+      while (todo != 0ull && ng < kBinGroups) {
+        const unsigned lkey = (unsigned)__builtin_amdgcn_readlane((int)key, __builtin_ctzll(todo));
+        const bool mine = key == lkey;
+        const unsigned long long m = __ballot(mine);
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        mygroup = mine ? ng : mygroup;
+        myrank = mine ? below : myrank;
+        gkey = lane == ng ? lkey : gkey;
+        gcnt = lane == ng ? (uint32_t)__popcll(m) : gcnt;
+        todo &= ~m;
+        ++ng;
+      }
+      auto add = [&](unsigned k, uint32_t n) -> uint32_t {
+        unsigned slot = (k * 2654435761u) >> 22;   // top 10 bits
+        for (int probe = 0; probe < kBinProbe; ++probe) {
+          const uint32_t was = atomicCAS(&hkey[slot], kBinEmpty, k);
+          if (was == kBinEmpty || was == k) return slot << 16 | atomicAdd(&hcnt[slot], n);
+          slot = (slot + 1) & (kBinHash - 1);
+        }
+        return kBinDirect | atomicAdd(&cnt[k], n);
+      };
+      uint32_t base = 0;
+      if (lane < ng) base = add(gkey, gcnt);
+      uint32_t c = __shfl(base, mygroup) + myrank;
+      if ((todo >> lane) & 1ull) c = add(key, 1u);
+      code[(it * S + s) * 256 + threadIdx.x] = c;
+    }
+  }
+  __syncthreads();
+  {
+    constexpr int V = kBinHash / 256;
+    uint32_t k[V], n[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      k[i] = hkey[threadIdx.x + i * 256];
+      n[i] = hcnt[threadIdx.x + i * 256];
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (k[i] != kBinEmpty) n[i] = atomicAdd(&cnt[k[i]], n[i]);
+#pragma unroll
+    for (int i = 0; i < V; ++i) hcnt[threadIdx.x + i * 256] = n[i];
+  }
+  __syncthreads();
+  const int nq = min(iters * S, nbricks - first);
+  uint32_t* out = rank + (int64_t)first * 256 + threadIdx.x;
+#pragma unroll 4
+  for (int q = 0; q < nq; ++q) {
+    const uint32_t c = code[q * 256 + threadIdx.x];
+    out[q * 256] = (c & kBinDirect) ? c & ~kBinDirect : hcnt[c >> 16] + (c & 0xffffu);
+  }
+}
+
+// Scatter: the same bricks write their particles' CIC records to entries[cur[key] + rank],
+// cur[key] being the key's first place.
+template <bool P2>
+__global__ void __launch_bounds__(256)
+k_bin_scatter(const float* __restrict__ disp, BinGeo g, const uint32_t* __restrict__ cur,
+              const uint32_t* __restrict__ rank, CicRec* __restrict__ entries) {
+  constexpr int S = kScatterBricks;
+  const int b0 = (int)xcd_block(blockIdx.x, gridDim.x) * S;
+  bool valid[S];
+  int ix[S], iy[S], iz[S];
+  float ux[S], uy[S], uz[S];
+  uint32_t rk[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    int64_t p = 0;
+    ix[s] = iy[s] = iz[s] = 0;
+    valid[s] = brick_particle<P2>(g, b0 + s, ix[s], iy[s], iz[s], p);
+    ux[s] = uy[s] = uz[s] = 0.f;
+    rk[s] = 0;
+    if (valid[s]) {
+      ux[s] = disp[p];
+      uy[s] = disp[g.N + p];
+      uz[s] = disp[2 * g.N + p];
+      rk[s] = rank[(int64_t)(b0 + s) * 256 + threadIdx.x];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    if (!valid[s]) continue;
+    CicRec rec;
+    const unsigned key = bin_key<P2>(g, ix[s], iy[s], iz[s], ux[s], uy[s], uz[s], rec);
+    entries[cur[key] + rk[s]] = rec;
   }
 }
 
@@ -336,6 +428,15 @@ __device__ __forceinline__ float fix_to_float(unsigned long long v) {
   return (float)(d * (1.0 / kFix));
 }
 
+// One tile.  Its particles come as a list: first its own class-0 particles, whose eight
+// corners all lie inside (most of them, contiguous in the sorted records), then the
+// segments whose corners need a test: its other classes and, from each lower neighbour
+// T - d, every class c with (c & d) == d.  A wave that holds class-0 particles only adds its
+// corners at constant offsets from one LDS address without tests, and the first of them are
+// loaded while the accumulator is cleared and the segment list built: 1.96 ms for 512^3
+// particles on 1024^3 cells, with every corner tested and every record looked up in the
+// list 2.02.  What is left is the latency of a tile (counts, records, stores: 7.6 us with
+// four tiles a CU; the LDS adds take 0.3 ms of the pass).
 template <int T>
 __global__ void __launch_bounds__(kDepositThreads)
 k_deposit_tiles(const CicRec* __restrict__ entries, const uint32_t* __restrict__ start,
@@ -350,10 +451,12 @@ k_deposit_tiles(const CicRec* __restrict__ entries, const uint32_t* __restrict__
   const int nt1 = g.nt1;
   const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
   const int tx = tile / (nt1 * nt1), ty = (tile / nt1) % nt1, tz = tile % nt1;
+  const uint32_t n0 = cnt[(int64_t)tile * 8], st0 = start[tile];
+  const CicRec* own = entries + st0;
+  CicRec r0{0u, 0u, 0u};
+  if (threadIdx.x < n0) r0 = own[threadIdx.x];
   for (int i = threadIdx.x; i < T * T * T; i += blockDim.x) acc[i] = 0ull;
-  // Flatten the (offset d, class c) segments that reach this tile into one list, so the
-  // entries are read in a single strided sweep: the whole own tile (d = 0) and, from the
-  // lower neighbour T - d, every class c with (c & d) == d (at most 1 + 19 segments).
+  // Flatten the segments after the own class-0 particles into one list (at most 1 + 19).
   // Wave 0 builds it with one lane per (d, c): class offsets inside the source tile by an
   // 8-lane scan, list positions by ballot, list offsets by a wave scan.
   __shared__ uint32_t sb[20], so[21];
@@ -363,16 +466,16 @@ k_deposit_tiles(const CicRec* __restrict__ entries, const uint32_t* __restrict__
     const int sx = (tx - (d & 1) + nt1) % nt1, sy = (ty - ((d >> 1) & 1) + nt1) % nt1,
               sz = (tz - ((d >> 2) & 1) + nt1) % nt1;
     const int64_t src = ((int64_t)sx * nt1 + sy) * nt1 + sz;
-    const uint32_t nc = cnt[src * 8 + c], st0 = start[src];
+    const uint32_t nc = cnt[src * 8 + c], st = start[src];
     uint32_t incl = nc;   // inclusive scan over the 8 classes of the source tile
 #pragma unroll
     for (int o = 1; o < 8; o <<= 1) {
       const uint32_t t = __shfl_up(incl, o, 8);
       if (c >= o) incl += t;
     }
-    const uint32_t tot = __shfl(incl, 7, 8);
-    const bool valid = d == 0 ? (c == 0 && tot > 0) : ((c & d) == d && nc > 0);
-    const uint32_t n = d == 0 ? tot : nc;
+    const uint32_t rest = __shfl(incl, 7, 8) - n0;   // of the own tile: classes 1 .. 7
+    const bool valid = d == 0 ? (c == 1 && rest > 0) : ((c & d) == d && nc > 0);
+    const uint32_t n = d == 0 ? rest : nc;
     const unsigned long long vm = __ballot(valid);
     const int pos = __popcll(vm & ((1ull << lane) - 1ull));
     uint32_t x = valid ? n : 0u;   // inclusive scan of the segment lengths over the wave
@@ -382,54 +485,76 @@ k_deposit_tiles(const CicRec* __restrict__ entries, const uint32_t* __restrict__
       if (lane >= o) x += t;
     }
     if (valid) {
-      sb[pos] = d == 0 ? st0 : st0 + incl - nc;
-      so[pos] = x - n;
+      sb[pos] = d == 0 ? st0 + n0 : st + incl - nc;
+      so[pos] = n0 + x - n;
       sdd[pos] = d;
     }
     if (lane == 63) {
       nseg = __popcll(vm);
-      so[__popcll(vm)] = x;
+      so[__popcll(vm)] = n0 + x;
     }
   }
   __syncthreads();
   const uint32_t total = so[nseg];
-  int sg = 0;
-  // batches of KB records per thread: all loads are issued before the LDS accumulation
-  constexpr int KB = 4;
-  for (uint32_t e0 = threadIdx.x; e0 < total; e0 += KB * blockDim.x) {
-    CicRec r[KB];
-    int dd[KB];
+  const float unit = mass * kFix;   // scaling by the power of two commutes with the roundings
+  // adds record r of source tile T - d (d < 0: none); the whole wave calls it
+  auto add = [&](const CicRec& r, int d) {
+    const int cx = (int)(r.x >> 28), cy = (int)(r.y >> 28), cz = (int)(r.z >> 28);
+    const float dx = rec_d(r.x), dy = rec_d(r.y), dz = rec_d(r.z);
+    const float wx[2] = {unit * (1.f - dx), unit * dx}, wy[2] = {1.f - dy, dy}, wz[2] = {1.f - dz, dz};
+    auto val = [&](int o) {
+      return (unsigned long long)__float2uint_rn(wx[o & 1] * wy[(o >> 1) & 1] * wz[(o >> 2) & 1]);
+    };
+    if (__all(d < 0 || (d == 0 && cx < T - 1 && cy < T - 1 && cz < T - 1))) {
+      if (d == 0) {
+        unsigned long long* at = acc + (cx * T + cy) * T + cz;
 #pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      const uint32_t e = e0 + k * blockDim.x;
-      dd[k] = -1;
-      r[k] = CicRec{0u, 0u, 0u};
-      if (e < total) {
-        while (so[sg + 1] <= e) ++sg;
-        dd[k] = sdd[sg];
-        r[k] = entries[sb[sg] + (e - so[sg])];
+        for (int o = 0; o < 8; ++o) atomicAdd(at + (o & 1) * T * T + ((o >> 1) & 1) * T + ((o >> 2) & 1), val(o));
       }
-    }
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      const int d = dd[k];
-      if (d < 0) continue;
+    } else if (d >= 0) {
       // the lower corner of a particle of tile T - d lies at (home-tile coordinate - T)
       // on every axis where d is set
-      const int lx0 = (int)(r[k].x >> 28) - ((d & 1) ? T : 0);
-      const int ly0 = (int)(r[k].y >> 28) - (((d >> 1) & 1) ? T : 0);
-      const int lz0 = (int)(r[k].z >> 28) - (((d >> 2) & 1) ? T : 0);
-      const float dx = rec_d(r[k].x), dy = rec_d(r[k].y), dz = rec_d(r[k].z);
-      const float wx[2] = {1.f - dx, dx}, wy[2] = {1.f - dy, dy}, wz[2] = {1.f - dz, dz};
+      const int lx0 = cx - ((d & 1) ? T : 0), ly0 = cy - (((d >> 1) & 1) ? T : 0),
+                lz0 = cz - (((d >> 2) & 1) ? T : 0);
 #pragma unroll
       for (int o = 0; o < 8; ++o) {
         const int lx = lx0 + (o & 1), ly = ly0 + ((o >> 1) & 1), lz = lz0 + ((o >> 2) & 1);
         if (lx >= 0 && lx < T && ly >= 0 && ly < T && lz >= 0 && lz < T)
-          atomicAdd(&acc[(lx * T + ly) * T + lz],
-                    (unsigned long long)__float2uint_rn(
-                        mass * wx[o & 1] * wy[(o >> 1) & 1] * wz[(o >> 2) & 1] * kFix));
+          atomicAdd(&acc[(lx * T + ly) * T + lz], val(o));
       }
     }
+  };
+  // the list's element e and its source
+  int sg = 0;
+  auto fetch = [&](uint32_t e, CicRec& r) -> int {
+    r = CicRec{0u, 0u, 0u};
+    if (e >= total) return -1;
+    if (e < n0) {
+      r = own[e];
+      return 0;
+    }
+    while (so[sg + 1] <= e) ++sg;
+    r = entries[sb[sg] + (e - so[sg])];
+    return sdd[sg];
+  };
+  // batches of KB records per thread: all loads are issued before the LDS accumulation
+  constexpr int KB = 4;
+  for (uint32_t e0 = 0; e0 < total; e0 += KB * kDepositThreads) {
+    CicRec r[KB];
+    int dd[KB];
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const uint32_t e = e0 + k * kDepositThreads + threadIdx.x;
+      if (k == 0 && e0 == 0 && e < n0) {
+        r[0] = r0;
+        dd[0] = 0;
+      } else {
+        dd[k] = fetch(e, r[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (e0 + k * kDepositThreads < total) add(r[k], dd[k]);   // uniform over the work-group
   }
   __syncthreads();
   // 16-byte stores: T, the row pitch and the plane stride are multiples of 4 floats
@@ -444,8 +569,9 @@ k_deposit_tiles(const CicRec* __restrict__ entries, const uint32_t* __restrict__
 }
 
 void launch_deposit(const Layout& L, const float* disp, float* rho, void* bins, void* entries_raw,
-                    hipStream_t s) {
+                    void* ranks, hipStream_t s) {
   CicRec* entries = static_cast<CicRec*>(entries_raw);
+  uint32_t* rank = static_cast<uint32_t*>(ranks);
   BinGeo g;
   g.np = L.np;
   g.nm = L.nm;
@@ -470,10 +596,13 @@ void launch_deposit(const Layout& L, const float* disp, float* rho, void* bins, 
     ProfScope ps("bin_count", s);
     hipLaunchKernelGGL(k_fill, dim3(grid_for(8 * L.ntiles, 256)), dim3(256), 0, s,
                        reinterpret_cast<float*>(cnt), 8 * L.ntiles, 0.f);
+    // more bricks a work-group means fewer global adds; 2048 work-groups still fill the chip
+    const int iters = (int)std::max<int64_t>(1, std::min<int64_t>(kBinIters, bricks / 2048));
+    const unsigned grid = (bricks + iters - 1) / iters;
     if (p2)
-      hipLaunchKernelGGL((k_bin<0, true>), dim3(bricks), dim3(256), 0, s, disp, g, cnt, cur, entries);
+      hipLaunchKernelGGL(k_bin_count<true>, dim3(grid), dim3(256), 0, s, disp, g, iters, cnt, rank, (int)nbricks);
     else
-      hipLaunchKernelGGL((k_bin<0, false>), dim3(bricks), dim3(256), 0, s, disp, g, cnt, cur, entries);
+      hipLaunchKernelGGL(k_bin_count<false>, dim3(grid), dim3(256), 0, s, disp, g, iters, cnt, rank, (int)nbricks);
     COLA_LAUNCH_CHECK();
   }
   {
@@ -486,10 +615,11 @@ void launch_deposit(const Layout& L, const float* disp, float* rho, void* bins, 
   }
   {
     ProfScope ps("bin_scatter", s);
+    const unsigned sgrid = (unsigned)((nbricks + kScatterBricks - 1) / kScatterBricks);
     if (p2)
-      hipLaunchKernelGGL((k_bin<1, true>), dim3(bricks), dim3(256), 0, s, disp, g, cnt, cur, entries);
+      hipLaunchKernelGGL(k_bin_scatter<true>, dim3(sgrid), dim3(256), 0, s, disp, g, cur, rank, entries);
     else
-      hipLaunchKernelGGL((k_bin<1, false>), dim3(bricks), dim3(256), 0, s, disp, g, cnt, cur, entries);
+      hipLaunchKernelGGL(k_bin_scatter<false>, dim3(sgrid), dim3(256), 0, s, disp, g, cur, rank, entries);
     COLA_LAUNCH_CHECK();
   }
   ProfScope ps("deposit", s);
