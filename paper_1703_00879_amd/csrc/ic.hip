@@ -227,13 +227,12 @@ __device__ __forceinline__ void growth_model(const GrowthDev& g, const MBSpline&
 // LDS: two reciprocals and about thirty FP64 operations per mode and point.
 //
 // What bounds it: up to about 10^5 modes (a wave or two per SIMD) the latency of one mode's
-// chain of steps, so few, wide steps whose four sequences advance independently; above
-// that the FP64 rate.  Measured on a whole table: 10.2 -> 0.24 ms for the 769 modes of 32^3
-// particles and 18.6 -> 0.41 ms for the 110593 of 384^3 (f(R), from z = 19, 10 and 30
-// slices), against fourth-order Runge-Kutta steps of 1e-3 that evaluated the model in full
-// for every mode and stage.  Steps of 0.04 hold the largest relative error of any table
-// entry at 1e-13 (the Runge-Kutta steps: 4e-13); it is truncation from 0.05 on, rounding
-// below.
+// chain of steps, so few, wide steps whose four sequences advance independently.  Measured
+// on a whole table from z = 19: LCDM, 64^3 particles, 10 slices, 6.5 -> 0.24 ms, against
+// fourth-order Runge-Kutta steps of 1e-3 that evaluated the model in full for every mode
+// and stage.  Steps of 0.04 hold the largest relative error of any table entry at 1e-13 (the
+// Runge-Kutta steps: 4e-13, 9e-12 for the symmetron); it is truncation from 0.05 on, rounding
+// below.  f(R) modes keep the Runge-Kutta steps (further below).
 constexpr double kGrowthStep = 0.04;     // longest step in ln a
 constexpr double kGradeFirst = 1e-10;    // after a_*: steps kGradeFirst + kGrade (ln a - ln a_*)
 constexpr double kGrade = 0.1;           // (error 3e-13; 0.2 gives 7e-13, 0.3 1e-11)
@@ -486,6 +485,219 @@ k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int 
   }
 }
 
+// ------------------------------------------------------------------ growth tables of f(R) modes
+// f(R) with its own growth has a table entry per mode and slice, up to 10^7 of them, each
+// rounded to FP32 for the step's LPT coefficients.  They come from fourth-order Runge-Kutta
+// steps <= 1e-3 in ln a, and keep those values to the last bit: an entry that rounds to
+// another FP32 value changes every particle of a run, if only in its last digits.  What is
+// shared is the model.  k_growth_fr_points evaluates the functions of a once per point;
+// k_growth_fr takes 64 modes a work-group and works through the steps in chunks of
+// kFrChunk as a pipeline of its waves,
+//   waves 1-3  kappa mu and the gamma_2 term of every mode at the chunk's points,
+//   wave 0     the Runge-Kutta steps of the chunk before,
+// a lane a mode, with one barrier a chunk.  The step's own chain of 76 FP64 operations bounds
+// small grids, the sum of the waves' operations large ones: 10.2 -> 0.55 ms for the 769
+// modes of 32^3 particles, 18.6 -> 2.6 ms for the 110593 of 384^3 (before, one thread a
+// mode evaluated the model in full at every stage).
+constexpr int kFrChunk = 10;
+constexpr int kFrPoints = 2 * kFrChunk + 2;   // start, (middle, end) a step, and the slice's a
+
+// Functions of a that do not depend on the mode, in the groupings the mode's terms take them;
+// r_hh and r_hE are the reciprocals of (a H0)^2 and a H0 E.
+struct FrPoint {
+  double f, kap, a2m2, c0, ahah, r_hh, ahE, r_hE, C0, X5Y4, G0, pad;
+};
+constexpr int kFrWords = sizeof(FrPoint) / sizeof(double2);
+
+// One integration: slices i at a_i, each reached from the one before in nsub equal steps.
+// Its points lie at off(i): the start, then (middle, end) of every step, then the slice's a.
+struct FrPlan {
+  double ai, l0;
+  int n_steps;
+  bool ref;   // the LCDM reference: one slice, at a = 1
+  __device__ __forceinline__ FrPlan(const GrowthDev& g, bool is_ref)
+      : ai(g.a_ini), l0(log(g.a_ini)), n_steps(g.n_steps), ref(is_ref) {}
+  __device__ __forceinline__ int slices() const { return ref ? 1 : n_steps + 1; }
+  __device__ __forceinline__ double a(int i) const { return ref ? 1.0 : ai + i * (1.0 - ai) / n_steps; }
+  __device__ __forceinline__ double from(int i) const { return i == 0 ? l0 : log(a(i - 1)); }
+  __device__ __forceinline__ int nsub(double lna, double le) const {
+    const int n = (int)ceil((le - lna) / 1e-3);
+    return n > 0 ? n : 0;
+  }
+  // a bound on the points of the slices before i (each needs 2 nsub + 2)
+  __device__ __forceinline__ int64_t off(int i) const {
+    return 2 * ((int64_t)((from(i) - l0) / 1e-3) + i) + 4 * (int64_t)i;
+  }
+};
+// points of both integrations: the bound off() takes at the end, twice over a's range
+static int64_t fr_points(const cola_params& p) {
+  return 4 * (int64_t)(std::min(std::log1p(p.z_init), 710.0) / 1e-3) + 6 * ((int64_t)p.n_steps + 4);
+}
+__device__ __forceinline__ int64_t fr_ref_base(const FrPlan& pl) {   // the reference's points follow
+  return 2 * ((int64_t)((log(1.0) - pl.l0) / 1e-3)) + 6 * ((int64_t)pl.n_steps + 2);
+}
+
+__global__ void __launch_bounds__(256) k_growth_fr_points(GrowthDev g, FrPoint* __restrict__ pts) {
+  const bool ref = blockIdx.x + 1 == gridDim.x;
+  const FrPlan pl(g, ref);
+  const int i = ref ? 0 : blockIdx.x;
+  FrPoint* out = pts + (ref ? fr_ref_base(pl) : pl.off(i));
+  const double lna0 = pl.from(i), le = log(pl.a(i));
+  const int nsub = pl.nsub(lna0, le);
+  const double h = (le - lna0) / nsub;
+  for (int e = blockIdx.y * blockDim.x + threadIdx.x; e < 2 * nsub + 2; e += gridDim.y * blockDim.x) {
+    const int j = e == 0 ? 0 : (e - 1) / 2;
+    double l = lna0;   // ln a of step j, added up step by step as the integration does
+#pragma unroll 16
+    for (int at = 0; at < j; ++at) l += h;
+    double x = l;
+    if (e > 0) x = (e & 1) ? l + 0.5 * h : l + h;
+    const double a = e == 2 * nsub + 1 ? pl.a(i) : exp(x);
+    const double E = dE(a, g.om);
+    FrPoint p;
+    p.kap = 1.5 * g.om * a;
+    p.f = 1.0 / (a * a * E);
+    const double ol = 1.0 - g.om;
+    const double X = g.om / (a * a * a) + 4.0 * ol, Y = g.om + 4.0 * ol;
+    const double r = X / Y;
+    p.a2m2 = a * a * kH0c * kH0c * Y * r * r * r / (2.0 * g.fr0);
+    p.c0 = X * X * X / (2.0 * g.fr0 * Y * Y);
+    const double ah = a * kH0c;
+    p.ahah = ah * ah;
+    p.r_hh = 1.0 / p.ahah;
+    p.ahE = ah * E;
+    p.r_hE = 1.0 / p.ahE;
+    p.C0 = -9.0 * g.om * g.om / (48.0 * ((a * a * a) * (a * a * a)) * g.fr0 * g.fr0);
+    p.X5Y4 = (X * X * X * X * X) / (Y * Y * Y * Y);
+    p.G0 = 2.0 * a * a * a * a * E * E;
+    p.pad = 0.0;
+    out[e] = p;
+  }
+}
+
+// x / d correctly rounded, from r = 1/d correctly rounded (Markstein's theorem: one corrected
+// product; no overflow or underflow in the ranges of k, a H0 and E)
+__device__ __forceinline__ double div_by(double x, double d, double r) {
+  const double q = x * r;
+  return fma(fma(-d, q, x), r, q);
+}
+
+__global__ void __launch_bounds__(256)
+k_growth_fr(GrowthDev g, SpecDev sp, const FrPoint* __restrict__ pts, double* __restrict__ table,
+            double* __restrict__ ref_out) {
+  __shared__ __align__(16) FrPoint pt[3][kFrPoints];
+  __shared__ double2 md[2][kFrPoints][64];   // (kappa mu, gamma_2 term) per mode
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (blockIdx.x + 1 == gridDim.x) {
+    if (wave == 0) {
+      const double A = sigma8_norm(sp);
+      if (lane == 0) ref_out[6] = A;
+    }
+    return;
+  }
+  const bool ref = blockIdx.x + 2 == gridDim.x;
+  const FrPlan pl(g, ref);
+  const int64_t t = ref ? g.n_k : blockIdx.x * (int64_t)64 + lane;
+  const double k = ref ? 0.0 : g.kf * sqrt((double)t), k2 = k * k;
+  double y[4];
+  {
+    const double g0 = pl.ai * pl.ai * dE(pl.ai, g.om);
+    y[0] = 1.0;
+    y[1] = g0;
+    y[2] = -3.0 / 7.0;
+    y[3] = -6.0 / 7.0 * g0;
+  }
+  int turn = 0;   // chunks begun: chunk n is in pt[n % 3] and md[n % 2]
+  // wave 0's work on a chunk of m steps (and its slice, if the chunk ends one)
+  auto integrate = [&](int n, int m, double h, int slice) {
+    const FrPoint* p = pt[n % 3];
+    const double2(*v)[64] = md[n % 2];
+    auto rhs = [&](double2 c, double f, const double* yy, double* dy) {
+      const double ds = yy[0];
+      dy[0] = yy[1] * f;
+      dy[1] = c.x * yy[0] * f;
+      dy[2] = yy[3] * f;
+      dy[3] = (c.x * yy[2] - c.x * ds * ds - c.y * ds * ds) * f;
+    };
+    double2 ca = v[0][lane];
+    double fa = p[0].f;
+    for (int j = 0; j < m; ++j) {
+      const double2 cb = v[2 * j + 1][lane], cc = v[2 * j + 2][lane];
+      const double fb = p[2 * j + 1].f, fc = p[2 * j + 2].f;
+      double k1[4], k2[4], k3[4], k4[4], yt[4];
+      rhs(ca, fa, y, k1);
+      for (int e = 0; e < 4; ++e) yt[e] = y[e] + 0.5 * h * k1[e];
+      rhs(cb, fb, yt, k2);
+      for (int e = 0; e < 4; ++e) yt[e] = y[e] + 0.5 * h * k2[e];
+      rhs(cb, fb, yt, k3);
+      for (int e = 0; e < 4; ++e) yt[e] = y[e] + h * k3[e];
+      rhs(cc, fc, yt, k4);
+      for (int e = 0; e < 4; ++e) y[e] += h / 6.0 * (k1[e] + 2.0 * k2[e] + 2.0 * k3[e] + k4[e]);
+      ca = cc;
+      fa = fc;
+    }
+    if (slice >= 0 && (ref ? lane == 0 : t < g.n_k)) {
+      const double2 c = v[2 * m + 1][lane];
+      const double ds = y[0];
+      double* out = ref ? ref_out : table + ((int64_t)slice * g.n_k + t) * 6;
+      out[0] = y[0];
+      out[1] = y[1];
+      out[2] = c.x * y[0];
+      out[3] = y[2];
+      out[4] = y[3];
+      out[5] = c.x * y[2] - c.x * ds * ds - c.y * ds * ds;
+    }
+  };
+  // points a chunk's first needs: start, then middle and end of its steps (and the slice's a)
+  auto stage = [&](int n, const FrPoint* src, int np) {   // all threads but wave 0's
+    const double2* s2 = reinterpret_cast<const double2*>(src);
+    double2* d2 = reinterpret_cast<double2*>(pt[n % 3]);
+    for (int e = threadIdx.x - 64; e < np * kFrWords; e += 192) d2[e] = s2[e];
+  };
+  // the chunk being formed and the one before it
+  int m_prev = 0, slice_prev = -1;
+  double h_prev = 0.0;
+  bool have_prev = false;
+  for (int i = 0; i < pl.slices(); ++i) {
+    const FrPoint* base = pts + (ref ? fr_ref_base(pl) : pl.off(i));
+    const double lna0 = pl.from(i), le = log(pl.a(i));
+    const int nsub = pl.nsub(lna0, le);
+    const double h = (le - lna0) / nsub;
+    for (int s = 0; s == 0 || s < nsub; s += kFrChunk) {
+      const int m = nsub - s < kFrChunk ? nsub - s : kFrChunk;
+      const bool last = s + m == nsub;
+      const int np = 2 * m + 1 + (last ? 1 : 0);
+      if (wave > 0) stage(turn, base + 2 * s, np);   // pt[turn % 3] was last read two chunks ago
+      __syncthreads();   // this chunk's points are staged; the chunk before is formed
+      if (wave > 0) {
+        for (int q = wave - 1; q < np; q += 3) {
+          const FrPoint p = pt[turn % 3][q];
+          double mu = 1.0, g2t = 0.0;
+          if (!ref) {
+            mu = 1.0 + k2 / (3.0 * (k2 + p.a2m2));
+            const double kk = div_by(k2, p.ahah, p.r_hh);
+            const double Pk = kk + p.c0;
+            const double Ph = 0.5 * kk + p.c0;   // halving is exact
+            const double kah = div_by(k, p.ahE, p.r_hE);
+            const double g2 = p.C0 * kah * kah * p.X5Y4 / (Pk * Ph * Ph);
+            g2t = p.G0 * g2;
+          }
+          md[turn % 2][q][lane] = make_double2(p.kap * mu, g2t);
+        }
+      } else if (have_prev) {
+        integrate(turn - 1, m_prev, h_prev, slice_prev);
+      }
+      have_prev = true;
+      m_prev = m;
+      h_prev = h;
+      slice_prev = last ? i : -1;
+      ++turn;
+    }
+  }
+  __syncthreads();   // the last chunk is formed
+  if (wave == 0) integrate(turn - 1, m_prev, h_prev, slice_prev);
+}
+
 // Step boundaries in ln a: every a_i, the knots of a tabulated {m, beta} model (the splines'
 // third derivatives jump there) and the symmetron's a_* are boundaries.  Just after a_*
 // the symmetron's gamma_2 term has a peak whose width in ln a scales as (k / (a_* m_*))^2,
@@ -534,6 +746,17 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
   g.kdep = L.kdep ? 1 : 0;
   g.n_steps = p.n_steps;
   g.n_k = L.n_k;
+  const SpecDev sp = spec_dev(p);
+  const size_t fr_bytes = (size_t)fr_points(p) * sizeof(FrPoint);
+  if (g.kdep && g.model == COLA_FR_HS1 && !(p.readings & COLA_READ_D2_HALF_K) &&
+      fr_bytes <= L.scratch_bytes) {
+    FrPoint* pts = static_cast<FrPoint*>(scratch);
+    hipLaunchKernelGGL(k_growth_fr_points, dim3(p.n_steps + 2, 16), dim3(256), 0, s, g, pts);   // + reference
+    const dim3 grid((unsigned)((L.n_k + 63) / 64) + 2), block(256);   // + reference, spectrum
+    hipLaunchKernelGGL(k_growth_fr, grid, block, 0, s, g, sp, pts, table, ref);
+    COLA_LAUNCH_CHECK();
+    return;
+  }
   const MBSpline mb = mb_spline(p);
   GrowthNode* nodes = static_cast<GrowthNode*>(scratch);
   int nsteps = 0;
@@ -587,7 +810,6 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
     lna = l1;
   }
   flush();
-  const SpecDev sp = spec_dev(p);
   const dim3 grid((unsigned)((L.n_k + 1 + 63) / 64) + 1), block(64);
   if (p.readings & COLA_READ_D2_HALF_K)
     hipLaunchKernelGGL(k_growth_ode<true>, grid, block, 0, s, g, sp, nodes, nsteps, table, ref);
