@@ -281,6 +281,11 @@ constexpr int kFirstFromLds = 1, kLastToLds = 2;
 // stage's when both have the same radix, so a following transform can take its first
 // operands from registers filled by this store.
 constexpr int kStoreIR = 4;
+// kPin: the last stage's outputs are complete before the first is stored.  Where store()
+// branches, the compiler otherwise moves an output's last addition behind the branch, away
+// from the product it would have been fused with, and the transform loses the bits that
+// a plain pass of the same plan has.
+constexpr int kPin = 8;
 
 template <int N, int DIR, int E, int B, int LS, int TWS, int S, int NS, int FL = 0,
           class P = Plan<N>>
@@ -328,6 +333,10 @@ struct GStages {
         }
         Dft<R, DIR>::run(v[i]);
         const int idxD = (j / NS) * NS * R + k;
+        if constexpr (S + 1 == nst && (FL & kPin) != 0) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) asm volatile("" : "+v"(v[i][r].x), "+v"(v[i][r].y));
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if constexpr (S + 1 == nst) {
@@ -406,7 +415,7 @@ k_fft_col(float2* __restrict__ data, int64_t elemStride, int64_t tilesPerBlock,
 
 // Forward X pass that bins the power of its modes into shells instead of writing them: the
 // field is read once where a plain pass and a binning kernel read it twice and wrote it
-// once (at n = 1024, 4.3 GB instead of 12.9: 2.3 ms, before 2.3 + 3.2; at 256 24 us, before 23 + 58).  A mode's term
+// once (at n = 1024, 4.3 GB instead of 12.9: 2.4 ms, before 2.3 + 3.2; at 256 27 us, before 23 + 58).  A mode's term
 // w vol (a_r^2 + a_i^2), a = delta_k / (n^3 W), is formed in FP32 in the transform's last stage
 // and added to the block's shell sums in LDS in FP64.  The lanes of a wave hold B adjacent
 // nu_z and a few adjacent nu_x, which meet few shells; where LDS leaves room, every kCopy-th
@@ -462,18 +471,12 @@ k_fft_col_pk(const float2* __restrict__ data, int64_t elemStride, int ntiles,
       const int n2 = __mul24(nx, nx) + n2yz;
       const int b = shell_of(n2);
       if (iz > h || n2 == 0 || b >= a.nbins) return;
-      // both quotients by W in [0.06, 1] from one reciprocal, each corrected by its residual
       const float W = wxx[i][r] * wy * wy * wz * wz;
-      const float r0 = fast_rcp(W), rW = fmaf(fmaf(-W, r0, 1.f), r0, r0);
-      auto quot = [&](float x) {
-        const float q = x * rW;
-        return fmaf(fmaf(-W, q, x), rW, q);
-      };
-      const float ar = quot(v.x * invM), ai = quot(v.y * invM);
+      const float ar = v.x * invM / W, ai = v.y * invM / W;
       atomicAdd(&sp[b * NC + c % NC], (double)((float)w * a.vol * (ar * ar + ai * ai)));
     };
     __syncthreads();   // the previous tile has left LDS (and before the first, the sums are cleared)
-    GStages<N, -1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
+    GStages<N, -1, E, B, B, 1, 0, 1, kStoreIR | kPin>::run(lds, tid, T, tw, load, store);
   }
   __syncthreads();
   for (int b = tid; b < a.nbins; b += T) {
