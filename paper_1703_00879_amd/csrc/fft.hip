@@ -125,16 +125,37 @@ struct Dft<8, DIR> {
 };
 
 // ------------------------------------------------------------------ plans
-// Radix plan and per-thread element count E for each supported transform length.
+// Radix plan and per-thread element count E for each supported transform length.  Where E
+// holds the product of the last two radices, those stages run as one pass through LDS
+// (kJoin): a thread takes the R1 R2 elements that are closed under both, so their
+// exchange stays in registers.  Every butterfly is the one the two passes would compute,
+// and so is every bit of the result; one round trip through LDS and two barriers go.
+// The row plans below take it (interleaved rows of three fields, with the padding there:
+// 384^3 3.26 -> 2.81 ms, 192^3 420 -> 342 us).  The column passes do not: the joined X
+// passes of 1024 were 9 to 54 % slower (registers).
 template <int N>
 struct Plan;
 #define COLA_PLAN(N_, E_, NST_, ...)                              \
   template <>                                                     \
   struct Plan<N_> {                                               \
     static constexpr int E = E_;                                  \
+    static constexpr bool join = false;                           \
     static constexpr int nst = NST_;                              \
     static constexpr int rad[NST_] = {__VA_ARGS__};               \
   };
+template <class P>
+constexpr int join_size() {
+  if constexpr (P::nst >= 2) return P::rad[P::nst - 2] * P::rad[P::nst - 1];
+  else return 0;
+}
+// E: the kernel's elements per thread (a row pass may take fewer than the plan)
+template <class P, int E>
+constexpr bool kJoin = P::join && join_size<P>() > 0 && E % (join_size<P>() > 0 ? join_size<P>() : 1) == 0;
+// Elements of one butterfly of the first and of the last pass through LDS.
+template <class P, int E>
+constexpr int kFirstRadix = kJoin<P, E> && P::nst == 2 ? join_size<P>() : P::rad[0];
+template <class P, int E>
+constexpr int kLastRadix = kJoin<P, E> ? join_size<P>() : P::rad[P::nst - 1];
 COLA_PLAN(4, 4, 1, 4)
 COLA_PLAN(6, 6, 2, 2, 3)
 COLA_PLAN(8, 8, 1, 8)
@@ -163,6 +184,7 @@ struct RowPlan : Plan<N> {};
   template <>                                                     \
   struct RowPlan<N_> {                                            \
     static constexpr int E = E_;                                  \
+    static constexpr bool join = true;                            \
     static constexpr int nst = NST_;                              \
     static constexpr int rad[NST_] = {__VA_ARGS__};               \
   };
@@ -176,8 +198,8 @@ COLA_ROW_PLAN(768, 12, 5, 4, 4, 4, 4, 3)
 #undef COLA_PLAN
 // First and last radix equal: a transform's last stage can hand its outputs to the next
 // transform's first stage in registers (kStoreIR).
-template <int N>
-constexpr bool kHandOff = Plan<N>::rad[0] == Plan<N>::rad[Plan<N>::nst - 1];
+template <int N, int E>
+constexpr bool kHandOff = kFirstRadix<Plan<N>, E> == kLastRadix<Plan<N>, E>;
 
 // Twiddle of operand r of butterfly k in the Stockham stage with NS = product of the
 // earlier radices.  TWS > 0: from the full table, tw[t * TWS] = exp(-2 pi i t / N) (the
@@ -213,13 +235,62 @@ __device__ __forceinline__ void fill_stage_twiddles(float2* tw, const float2* __
   }
 }
 
+// Butterfly k (mod NS) of stage S, with its twiddles; JOIN: of stages S and S + 1 together, on
+// the radix R1 R2 operands v[s + R2 r] (operand r of the R1-point butterfly s), leaving
+// output r2 of the R2-point butterfly r1 in v[r1 + R1 r2].  As a stage of radix R1 R2 a joined
+// butterfly reads and writes the elements that the two stages would.
+template <int N, class P, int S, int NS, int DIR, int TWS, bool JOIN>
+__device__ __forceinline__ void butterfly(float2* v, int k, const float2* __restrict__ tw) {
+  constexpr int R1 = P::rad[S];
+  auto twiddled = [&](float2 x, auto stage_ns, auto radix, int kk, int r) -> float2 {
+    constexpr int ns = decltype(stage_ns)::value, R = decltype(radix)::value;
+    float2 w = stage_twiddle<N, R, ns, TWS>(tw, kk, r);
+    if (DIR > 0) w.y = -w.y;
+    return cmul(x, w);
+  };
+  if constexpr (!JOIN) {
+    if (NS > 1) {
+#pragma unroll
+      for (int r = 1; r < R1; ++r)
+        v[r] = twiddled(v[r], std::integral_constant<int, NS>{}, std::integral_constant<int, R1>{}, k, r);
+    }
+    Dft<R1, DIR>::run(v);
+  } else {
+    constexpr int R2 = P::rad[S + 1];
+    float2 y[R2][R1];
+#pragma unroll
+    for (int s = 0; s < R2; ++s) {
+#pragma unroll
+      for (int r = 0; r < R1; ++r) {
+        y[s][r] = v[s + R2 * r];
+        if (NS > 1 && r > 0)
+          y[s][r] = twiddled(y[s][r], std::integral_constant<int, NS>{}, std::integral_constant<int, R1>{}, k, r);
+      }
+      Dft<R1, DIR>::run(y[s]);
+    }
+#pragma unroll
+    for (int r1 = 0; r1 < R1; ++r1) {
+      float2 z[R2];
+      z[0] = y[0][r1];
+#pragma unroll
+      for (int s = 1; s < R2; ++s)
+        z[s] = twiddled(y[s][r1], std::integral_constant<int, NS * R1>{}, std::integral_constant<int, R2>{},
+                        k + r1 * NS, s);
+      Dft<R2, DIR>::run(z);
+#pragma unroll
+      for (int r2 = 0; r2 < R2; ++r2) v[r1 + R1 * r2] = z[r2];
+    }
+  }
+}
+
 // One Stockham stage of radix R on B transforms of length N held in LDS as
 // lds[j * LS + c] (element j of transform c).  Butterfly b = tid + i*T maps to
 // column c = b % B (fastest, so lanes touch consecutive LDS words) and index j = b / B.
 // All operands are read into registers before the barrier, so the stage is in place.
 // Twiddles: tw[t * TWS] = exp(-2 pi i t / N).
-template <int N, int R, int NS, int DIR, int E, int B, int LS, int TWS>
+template <int N, class P, int S, int NS, int DIR, int E, int B, int LS, int TWS, bool JOIN>
 __device__ __forceinline__ void stockham_stage(float2* lds, int tid, int T, const float2* __restrict__ tw) {
+  constexpr int R = JOIN ? join_size<P>() : P::rad[S];
   constexpr int NB = E / R;
   float2 v[NB][R];
 #pragma unroll
@@ -235,15 +306,7 @@ __device__ __forceinline__ void stockham_stage(float2* lds, int tid, int T, cons
     const int b = tid + i * T;
     const int c = b % B, j = b / B;
     const int k = j % NS;
-    if (NS > 1) {
-#pragma unroll
-      for (int r = 1; r < R; ++r) {
-        float2 w = stage_twiddle<N, R, NS, TWS>(tw, k, r);
-        if (DIR > 0) w.y = -w.y;
-        v[i][r] = cmul(v[i][r], w);
-      }
-    }
-    Dft<R, DIR>::run(v[i]);
+    butterfly<N, P, S, NS, DIR, TWS, JOIN>(v[i], k, tw);
     const int idxD = (j / NS) * NS * R + k;
 #pragma unroll
     for (int r = 0; r < R; ++r) lds[(idxD + r * NS) * LS + c] = v[i][r];
@@ -255,9 +318,9 @@ template <int N, int DIR, int E, int B, int LS, int TWS, int S, int NS, class P>
 struct Stages {
   static __device__ __forceinline__ void run(float2* lds, int tid, int T, const float2* tw) {
     if constexpr (S < P::nst) {
-      constexpr int R = P::rad[S];
-      stockham_stage<N, R, NS, DIR, E, B, LS, TWS>(lds, tid, T, tw);
-      Stages<N, DIR, E, B, LS, TWS, S + 1, NS * R, P>::run(lds, tid, T, tw);
+      constexpr bool JOIN = kJoin<P, E> && S + 2 == P::nst;
+      stockham_stage<N, P, S, NS, DIR, E, B, LS, TWS, JOIN>(lds, tid, T, tw);
+      Stages<N, DIR, E, B, LS, TWS, S + (JOIN ? 2 : 1), NS * P::rad[S], P>::run(lds, tid, T, tw);
     }
   }
 };
@@ -295,11 +358,13 @@ struct GStages {
                                              Load& load, Store& store) {
     constexpr int nst = P::nst;
     if constexpr (S < nst) {
-      constexpr int R = P::rad[S];
+      constexpr bool JOIN = kJoin<P, E> && S + 2 == nst;
+      constexpr bool LAST = JOIN || S + 1 == nst;
+      constexpr int R = JOIN ? join_size<P>() : P::rad[S];
       constexpr int NB = E / R;
       float2 v[NB][R];
       constexpr bool reads_lds = S > 0 || (FL & kFirstFromLds);
-      constexpr bool writes_lds = S + 1 < nst || (FL & kLastToLds);
+      constexpr bool writes_lds = !LAST || (FL & kLastToLds);
       if constexpr (S == 0) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -323,23 +388,15 @@ struct GStages {
         const int b = tid + i * T;
         const int c = b % B, j = b / B;
         const int k = j % NS;
-        if (NS > 1) {
-#pragma unroll
-          for (int r = 1; r < R; ++r) {
-            float2 w = stage_twiddle<N, R, NS, TWS>(tw, k, r);
-            if (DIR > 0) w.y = -w.y;
-            v[i][r] = cmul(v[i][r], w);
-          }
-        }
-        Dft<R, DIR>::run(v[i]);
+        butterfly<N, P, S, NS, DIR, TWS, JOIN>(v[i], k, tw);
         const int idxD = (j / NS) * NS * R + k;
-        if constexpr (S + 1 == nst && (FL & kPin) != 0) {
+        if constexpr (LAST && (FL & kPin) != 0) {
 #pragma unroll
           for (int r = 0; r < R; ++r) asm volatile("" : "+v"(v[i][r].x), "+v"(v[i][r].y));
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          if constexpr (S + 1 == nst) {
+          if constexpr (LAST) {
             if constexpr ((FL & kStoreIR) != 0)
               store(idxD + r * NS, c, v[i][r], i, r);
             else
@@ -349,7 +406,7 @@ struct GStages {
           }
         }
       }
-      if constexpr (S + 1 < nst) {
+      if constexpr (!LAST) {
         __syncthreads();
         GStages<N, DIR, E, B, LS, TWS, S + 1, NS * R, FL, P>::run(lds, tid, T, tw, load, store);
       }
@@ -435,7 +492,7 @@ k_fft_col_pk(const float2* __restrict__ data, int64_t elemStride, int ntiles,
              const float2* __restrict__ tw_g, PkBin a) {
   constexpr int B = PkCfg<N>::B, E = PkCfg<N>::E, T = PkCfg<N>::T;
   constexpr int NSH = PkCfg<N>::kShells, NC = PkCfg<N>::kCopy;
-  constexpr int RL = Plan<N>::rad[Plan<N>::nst - 1], NBL = E / RL;
+  constexpr int RL = kLastRadix<Plan<N>, E>, NBL = E / RL;
   static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
@@ -534,10 +591,10 @@ k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t el
   const int iy = col / op.pitch, iz = col % op.pitch;
   auto load = [&](int, int, int j, int c) -> float2 { return data[base + (O)j * es + c]; };
   auto store2 = [&](int j, int c, float2 v) { out[base + (O)j * es + c] = v; };
-  if constexpr (kHandOff<N>) {
+  if constexpr (kHandOff<N, E>) {
     // the operator is applied in the forward transform's last stage and the inverse
     // starts from those registers
-    constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
+    constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
     float2 hv[NB0][R0];
     auto store = [&](int j, int c, float2 v, int i, int r) {
       if (KEEP) data[base + (O)j * es + c] = v;
@@ -580,7 +637,7 @@ k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
     op.g_5 = op.step_newton ? 0.f : sd.g_5;
     op.a2m2 = op.step_newton ? 0.f : sd.a2m2;
   }
-  constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
+  constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
   static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
@@ -604,7 +661,7 @@ k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
     }
   }
   auto load = [&](int, int, int j, int c) -> float2 { return load_stream(src + base + (O)j * es + c); };
-  if constexpr (!DK && kHandOff<N>) {
+  if constexpr (!DK && kHandOff<N, E>) {
     // one source: g is formed in the forward transform's last stage, in registers
     auto store = [&](int jj, int, float2 v, int i, int r) { g[i][r] = green_force(op, jj, iy, iz, v, v); };
     GStages<N, -1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
@@ -648,7 +705,7 @@ k_fft_col_inv_yz(const float2* data, float2* outA, float2* __restrict__ outB, in
                  int64_t tilesPerBlock, int64_t blockStride, const float2* __restrict__ tw_g,
                  KOp op) {
   constexpr int B = ColCfg<N>::B, E = FusedCfg<N, B>::E, T = FusedCfg<N, B>::T;
-  constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
+  constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
   static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
@@ -709,7 +766,7 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
               float2* __restrict__ o0, float2* __restrict__ o1, int64_t elemStride,
               const float2* __restrict__ tw_g, KOp op) {
   constexpr int B = LptXCfg<N>::B, E = LptXCfg<N>::E, T = LptXCfg<N>::T;
-  constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
+  constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
   static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
@@ -1014,6 +1071,10 @@ k_fft_c2r_row3(const float2* __restrict__ in0, const float2* __restrict__ in1,
   constexpr int kN = 2 * NC;
   constexpr int kRowF = 3 * kN;   // floats per interleaved row (a multiple of 4)
   static_assert(kRowF % 4 == 0, "interleaved rows must hold whole float4s");
+  // LDS stride of an interleaved row.  3 n is a multiple of the 64 banks from n = 64 on, and
+  // the lanes that store hold B rows at the same cell; four floats more a row put the
+  // rows on different banks and keep them 16-byte aligned (where the tiles have the room).
+  constexpr int kRowS = (B > 1 && B * (kRowF + 4) <= 3 * 2 * NC * LS) ? kRowF + 4 : kRowF;
   __shared__ __align__(16) float2 lds[3][NC * LS];   // also read as float4 at the end
   __shared__ float2 tw[2 * NC];   // split twiddles, then the per-stage table (row_twiddles)
   const int tid = threadIdx.x;
@@ -1037,7 +1098,7 @@ k_fft_c2r_row3(const float2* __restrict__ in0, const float2* __restrict__ in1,
   // row c of component t holds cells (2m, 2m + 1), at floats 3 (2m) + t and 3 (2m + 1) + t
   // of the row.  The rows then leave as one contiguous block of 16-byte stores.
   float* ilv = reinterpret_cast<float*>(&lds[0][0]);
-  static_assert(B * kRowF <= 3 * 2 * NC * LS, "interleaved rows must fit the three tiles");
+  static_assert(B * kRowS <= 3 * 2 * NC * LS, "interleaved rows must fit the three tiles");
   for (; blk < nblk; blk += gridDim.x) {
     const O r0 = (O)blk * B;
     __syncthreads();   // twiddles staged; the previous block's rows have left the tiles
@@ -1047,7 +1108,7 @@ k_fft_c2r_row3(const float2* __restrict__ in0, const float2* __restrict__ in1,
     {
       auto load = [&](int, int, int j, int c) -> float2 { return tile[j * LS + c]; };
       auto store = [&](int m, int c, float2 v) {
-        float* rowp = ilv + c * kRowF + 6 * m + comp;
+        float* rowp = ilv + c * kRowS + 6 * m + comp;
         rowp[0] = v.x;
         rowp[3] = v.y;
       };
@@ -1058,7 +1119,7 @@ k_fft_c2r_row3(const float2* __restrict__ in0, const float2* __restrict__ in1,
     const int nq = (int)rows_here * (kRowF / 4);
     float4* dst = reinterpret_cast<float4*>(out + (O3)r0 * kRowF);
     const float4* src4 = reinterpret_cast<const float4*>(ilv);
-    for (int q = tid; q < nq; q += T) dst[q] = src4[q];
+    for (int q = tid; q < nq; q += T) dst[q] = src4[q + q / (kRowF / 4) * ((kRowS - kRowF) / 4)];
   }
 }
 
@@ -1111,8 +1172,8 @@ k_fft_screen_row(float2* __restrict__ data, const float* __restrict__ rho, float
   // radix RL.  Its density pair (x_2m, x_2m+1) is loaded with the row, so that the
   // latency hides behind the inverse transform.
   using RP = RowPlan<NC>;
-  constexpr int RL = RP::rad[RP::nst - 1], NBL = E / RL;
-  constexpr bool kHandOff = RL == RP::rad[0];
+  constexpr int RL = kLastRadix<RP, E>, NBL = E / RL;
+  constexpr bool handOff = RL == kFirstRadix<RP, E>;
   // Persistent: the work-group takes row blocks blockIdx.x, + gridDim.x, ...; the field
   // and density rows of the next block are loaded into registers while this block is
   // transformed and stored.
@@ -1165,7 +1226,7 @@ k_fft_screen_row(float2* __restrict__ data, const float* __restrict__ rho, float
         reinterpret_cast<float2*>(s_out + 2 * rb.off(c))[m] = make_float2(dl.x * e0, dl.y * e1);
       return make_float2(dl.x * (cn + c5 * e0), dl.y * (cn + c5 * e1));
     };
-    if constexpr (kHandOff) {
+    if constexpr (handOff) {
       // the last inverse stage hands its outputs to the first forward stage in registers
       float2 tv[NBL][RL];
       {
