@@ -130,30 +130,29 @@ struct Dft<8, DIR> {
 // (kJoin): a thread takes the R1 R2 elements that are closed under both, so their
 // exchange stays in registers.  Every butterfly is the one the two passes would compute,
 // and so is every bit of the result; one round trip through LDS and two barriers go.
-// The row plans below take it (interleaved rows of three fields, with the padding there:
-// 384^3 3.26 -> 2.81 ms, 192^3 420 -> 342 us).  The column passes do not: the joined X
-// passes of 1024 were 9 to 54 % slower (registers).
+// Up to 16 elements: a joined (8, 3) or (8, 4) is compiled to other fused multiply-adds and
+// differs in last digits (lengths 24, 192, 1536 and 2048; with two stages in all, 12 and
+// 24 too, hence three at least).  Gained: 3 to 13 % in the column passes (two-component Y pass
+// of 384^3 154 -> 136 us, of 1024^3 2.84 -> 2.61 ms; force X pass of 1024^3 5.14 -> 4.85 ms)
+// and, with the padded rows, the three-field row pass of 384^3 3.26 -> 2.81 ms.
 template <int N>
 struct Plan;
 #define COLA_PLAN(N_, E_, NST_, ...)                              \
   template <>                                                     \
   struct Plan<N_> {                                               \
     static constexpr int E = E_;                                  \
-    static constexpr bool join = false;                           \
     static constexpr int nst = NST_;                              \
     static constexpr int rad[NST_] = {__VA_ARGS__};               \
   };
 template <class P>
 constexpr int join_size() {
-  if constexpr (P::nst >= 2) return P::rad[P::nst - 2] * P::rad[P::nst - 1];
-  else return 0;
+  if constexpr (P::nst >= 3) return P::rad[P::nst - 2] * P::rad[P::nst - 1];
+  else return 32;
 }
 // E: the kernel's elements per thread (a row pass may take fewer than the plan)
 template <class P, int E>
-constexpr bool kJoin = P::join && join_size<P>() > 0 && E % (join_size<P>() > 0 ? join_size<P>() : 1) == 0;
-// Elements of one butterfly of the first and of the last pass through LDS.
-template <class P, int E>
-constexpr int kFirstRadix = kJoin<P, E> && P::nst == 2 ? join_size<P>() : P::rad[0];
+constexpr bool kJoin = join_size<P>() <= 16 && E % join_size<P>() == 0;
+// Elements of one butterfly of the last pass through LDS.
 template <class P, int E>
 constexpr int kLastRadix = kJoin<P, E> ? join_size<P>() : P::rad[P::nst - 1];
 COLA_PLAN(4, 4, 1, 4)
@@ -184,7 +183,6 @@ struct RowPlan : Plan<N> {};
   template <>                                                     \
   struct RowPlan<N_> {                                            \
     static constexpr int E = E_;                                  \
-    static constexpr bool join = true;                            \
     static constexpr int nst = NST_;                              \
     static constexpr int rad[NST_] = {__VA_ARGS__};               \
   };
@@ -199,7 +197,7 @@ COLA_ROW_PLAN(768, 12, 5, 4, 4, 4, 4, 3)
 // First and last radix equal: a transform's last stage can hand its outputs to the next
 // transform's first stage in registers (kStoreIR).
 template <int N, int E>
-constexpr bool kHandOff = kFirstRadix<Plan<N>, E> == kLastRadix<Plan<N>, E>;
+constexpr bool kHandOff = Plan<N>::rad[0] == kLastRadix<Plan<N>, E>;
 
 // Twiddle of operand r of butterfly k in the Stockham stage with NS = product of the
 // earlier radices.  TWS > 0: from the full table, tw[t * TWS] = exp(-2 pi i t / N) (the
@@ -439,6 +437,40 @@ struct XCfg {
   static constexpr int B = (N == 512 || N == 1024) ? 8 : ColCfg<N>::B;
 };
 
+// Elements of a tile of B columns: a thread's first- and last-stage elements are
+// j = tid / B + (a number known to the whole work-group), so an address is a scalar base plus
+// 32 bits of the thread's own, the form that global loads and stores take as it is.  Left
+// to itself the compiler forms a 64-bit address in vector registers for every element (it
+// widens the thread's part in another block, where instruction selection does not see it;
+// the empty asm keeps it 32 bits wide up to the access): about 100 instructions and 30
+// registers of the 1024-point force pass, which spilled 96 to 120 bytes a lane and now 0 to
+// 20.  Force X pass 1024^3 5.65 -> 5.14 ms, 512^3 587 -> 465 us, 192^3 34 -> 26; two-component
+// Y pass 192^3 25 -> 20; LPT X pass 192^3 69 -> 52, 384^3 422 -> 363; operator X pass 384^3
+// 165 -> 145.  The single-transform passes have the registers and stay as they are (1 to 5 %
+// slower with it at 96 to 384 points).
+template <int N, int B, int E, class O>
+struct ColTile {
+  static constexpr int T = N * B / E;
+  static_assert(T % B == 0, "a thread's butterflies must share one column");
+  static constexpr int RF = Plan<N>::rad[0], RL = kLastRadix<Plan<N>, E>;
+  O base, es;
+  unsigned thread;   // bytes; at most 64 planes of 2048^2 / 2 values
+  __device__ __forceinline__ ColTile(O base_, O es_, int tid)
+      : base(base_), es(es_), thread((unsigned)((tid / B) * es_ + tid % B) * 8u) {}
+  template <class V>
+  __device__ __forceinline__ V* at(V* p, int j) const {
+    typedef typename std::conditional<std::is_const<V>::value, const char, char>::type C;
+    unsigned t = thread;
+    asm volatile("" : "+v"(t));
+    return reinterpret_cast<V*>(reinterpret_cast<C*>(p + ((uint64_t)base + (uint64_t)j * es)) + t);
+  }
+  // operand r of butterfly i of the first stage, output r of butterfly i of the last
+  template <class V>
+  __device__ __forceinline__ V* first(V* p, int i, int r) const { return at(p, i * (T / B) + r * (N / RF)); }
+  template <class V>
+  __device__ __forceinline__ V* last(V* p, int i, int r) const { return at(p, i * (T / B) + r * (N / RL)); }
+};
+
 template <int N, int DIR, int KIND, int BB = ColCfg<N>::B>
 __global__ void __launch_bounds__(N * BB / ColCfg<N>::E)
 k_fft_col(float2* __restrict__ data, int64_t elemStride, int64_t tilesPerBlock,
@@ -472,7 +504,7 @@ k_fft_col(float2* __restrict__ data, int64_t elemStride, int64_t tilesPerBlock,
 
 // Forward X pass that bins the power of its modes into shells instead of writing them: the
 // field is read once where a plain pass and a binning kernel read it twice and wrote it
-// once (at n = 1024, 4.3 GB instead of 12.9: 2.4 ms, before 2.3 + 3.2; at 256 27 us, before 23 + 58).  A mode's term
+// once (at n = 1024, 4.3 GB instead of 12.9: 1.8 ms, before 2.3 + 3.2; at 256 22 us, before 23 + 58).  A mode's term
 // w vol (a_r^2 + a_i^2), a = delta_k / (n^3 W), is formed in FP32 in the transform's last stage
 // and added to the block's shell sums in LDS in FP64.  The lanes of a wave hold B adjacent
 // nu_z and a few adjacent nu_x, which meet few shells; where LDS leaves room, every kCopy-th
@@ -493,7 +525,6 @@ k_fft_col_pk(const float2* __restrict__ data, int64_t elemStride, int ntiles,
   constexpr int B = PkCfg<N>::B, E = PkCfg<N>::E, T = PkCfg<N>::T;
   constexpr int NSH = PkCfg<N>::kShells, NC = PkCfg<N>::kCopy;
   constexpr int RL = kLastRadix<Plan<N>, E>, NBL = E / RL;
-  static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
   __shared__ double sp[NSH * NC];
@@ -522,7 +553,8 @@ k_fft_col_pk(const float2* __restrict__ data, int64_t elemStride, int ntiles,
     const int n2yz = ny * ny + iz * iz;
     const float wy = a.wtab[ny < 0 ? -ny : ny], wz = a.wtab[iz <= h ? iz : 0];
     const unsigned w = (iz > 0 && iz < h) ? 2u : 1u;
-    auto load = [&](int, int, int j, int c) -> float2 { return load_stream(data + base + (O)j * es + c); };
+    const ColTile<N, B, E, O> io(base, es, tid);
+    auto load = [&](int i, int r, int, int) -> float2 { return load_stream(io.first(data, i, r)); };
     auto store = [&](int j, int c, float2 v, int i, int r) {
       const int nx = j < h ? j : j - N;
       const int n2 = __mul24(nx, nx) + n2yz;
@@ -576,11 +608,11 @@ struct OpCfg {
 
 template <int N, int KIND, bool KEEP>
 __global__ void __launch_bounds__(OpCfg<N>::T)
+__attribute__((amdgpu_waves_per_eu(N == 1024 ? 4 : 1)))
 k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t elemStride,
                  const float2* __restrict__ tw_g, KOp op) {
   constexpr int B = OpCfg<N>::B, E = OpCfg<N>::E, T = OpCfg<N>::T;
   if (op.steps) op.g_n = step_entry(op.steps, op.step_ctr).sop_g_n;
-  static_assert(T % B == 0, "a thread's butterflies must share one column");
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
   const int tid = threadIdx.x;
@@ -589,30 +621,31 @@ k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t el
   const O base = (O)xcd_block(blockIdx.x, gridDim.x) * B, es = (O)elemStride;
   const int col = (int)base + tid % B;   // (y, z) column of every element this thread touches
   const int iy = col / op.pitch, iz = col % op.pitch;
-  auto load = [&](int, int, int j, int c) -> float2 { return data[base + (O)j * es + c]; };
-  auto store2 = [&](int j, int c, float2 v) { out[base + (O)j * es + c] = v; };
+  const ColTile<N, B, E, O> io(base, es, tid);
+  auto load = [&](int i, int r, int, int) -> float2 { return *io.first(data, i, r); };
+  auto store2 = [&](int, int, float2 v, int i, int r) { *io.last(out, i, r) = v; };
   if constexpr (kHandOff<N, E>) {
     // the operator is applied in the forward transform's last stage and the inverse
     // starts from those registers
-    constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
+    constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
     float2 hv[NB0][R0];
-    auto store = [&](int j, int c, float2 v, int i, int r) {
-      if (KEEP) data[base + (O)j * es + c] = v;
+    auto store = [&](int j, int, float2 v, int i, int r) {
+      if (KEEP) *io.last(data, i, r) = v;
       hv[i][r] = kspace_apply<KIND>(op, j, iy, iz, v, v);
     };
     GStages<N, -1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();   // every thread has read its last operands out of the tile
     auto load2 = [&](int i, int r, int, int) -> float2 { return hv[i][r]; };
-    GStages<N, +1, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load2, store2);
+    GStages<N, +1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load2, store2);
   } else {
-    auto store = [&](int j, int c, float2 v) {
-      if (KEEP) data[base + (O)j * es + c] = v;
+    auto store = [&](int j, int c, float2 v, int i, int r) {
+      if (KEEP) *io.last(data, i, r) = v;
       lds[j * B + c] = kspace_apply<KIND>(op, j, iy, iz, v, v);
     };
-    GStages<N, -1, E, B, B, 1, 0, 1, kLastToLds>::run(lds, tid, T, tw, load, store);
+    GStages<N, -1, E, B, B, 1, 0, 1, kLastToLds | kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();
     auto load2 = [&](int, int, int j, int c) -> float2 { return lds[j * B + c]; };
-    GStages<N, +1, E, B, B, 1, 0, 1, kFirstFromLds>::run(lds, tid, T, tw, load2, store2);
+    GStages<N, +1, E, B, B, 1, 0, 1, kFirstFromLds | kStoreIR>::run(lds, tid, T, tw, load2, store2);
   }
 }
 
@@ -637,8 +670,7 @@ k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
     op.g_5 = op.step_newton ? 0.f : sd.g_5;
     op.a2m2 = op.step_newton ? 0.f : sd.a2m2;
   }
-  constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
-  static_assert(T % B == 0, "a thread's butterflies must share one column");
+  constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
   const int tid = threadIdx.x;
@@ -648,19 +680,18 @@ k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
   const int c0 = tid % B;
   const int col = (int)base + c0;
   const int iy = col / op.pitch, iz = col % op.pitch;
+  const ColTile<N, B, E, O> io(base, es, tid);
   float2 g[NB0][R0];
   if constexpr (DK) {
     // delta_k of the thread's elements, loaded with S's (same element map as the first
     // stage) so that both reads are in flight together; g takes them until the Green's
     // function replaces them
 #pragma unroll
-    for (int i = 0; i < NB0; ++i) {
-      const int j = (tid + i * T) / B;
+    for (int i = 0; i < NB0; ++i)
 #pragma unroll
-      for (int r = 0; r < R0; ++r) g[i][r] = load_stream(dk + base + (O)(j + r * (N / R0)) * es + c0);
-    }
+      for (int r = 0; r < R0; ++r) g[i][r] = load_stream(io.first(dk, i, r));
   }
-  auto load = [&](int, int, int j, int c) -> float2 { return load_stream(src + base + (O)j * es + c); };
+  auto load = [&](int i, int r, int, int) -> float2 { return load_stream(io.first(src, i, r)); };
   if constexpr (!DK && kHandOff<N, E>) {
     // one source: g is formed in the forward transform's last stage, in registers
     auto store = [&](int jj, int, float2 v, int i, int r) { g[i][r] = green_force(op, jj, iy, iz, v, v); };
@@ -688,8 +719,8 @@ k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
     auto load = [&](int i, int r, int jj, int) -> float2 {
       return t == 0 ? grad_minus_i(op, jj, iy, iz, 0, g[i][r]) : g[i][r];
     };
-    auto store = [&](int j, int c, float2 v) { store_stream(out + base + (O)j * es + c, v); };
-    GStages<N, +1, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load, store);
+    auto store = [&](int, int, float2 v, int i, int r) { store_stream(io.last(out, i, r), v); };
+    GStages<N, +1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();   // the second transform reuses the LDS tile
   }
 }
@@ -705,8 +736,7 @@ k_fft_col_inv_yz(const float2* data, float2* outA, float2* __restrict__ outB, in
                  int64_t tilesPerBlock, int64_t blockStride, const float2* __restrict__ tw_g,
                  KOp op) {
   constexpr int B = ColCfg<N>::B, E = FusedCfg<N, B>::E, T = FusedCfg<N, B>::T;
-  constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
-  static_assert(T % B == 0, "a thread's butterflies must share one column");
+  constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
   const int tid = threadIdx.x;
@@ -719,27 +749,26 @@ k_fft_col_inv_yz(const float2* data, float2* outA, float2* __restrict__ outB, in
   const O es = (O)elemStride;
   const int c0 = tid % B;
   const int iz = (int)colInBlock + c0;   // Y pass: the column is z
+  const ColTile<N, B, E, O> io(base, es, tid);
   float2 gv[NB0][R0];
 #pragma unroll
-  for (int i = 0; i < NB0; ++i) {
-    const int j = (tid + i * T) / B;
+  for (int i = 0; i < NB0; ++i)
 #pragma unroll
-    for (int r = 0; r < R0; ++r) gv[i][r] = data[base + (O)(j + r * (N / R0)) * es + c0];
-  }
+    for (int r = 0; r < R0; ++r) gv[i][r] = *io.first(data, i, r);
   {
     auto load = [&](int i, int r, int jj, int) -> float2 {
       return grad_minus_i(op, 0, jj, iz, 1, gv[i][r]);
     };
-    auto store = [&](int j, int c, float2 v) { outA[base + (O)j * es + c] = v; };
-    GStages<N, +1, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load, store);
+    auto store = [&](int, int, float2 v, int i, int r) { *io.last(outA, i, r) = v; };
+    GStages<N, +1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
   }
   __syncthreads();   // the second transform reuses the LDS tile
   {
     auto load = [&](int i, int r, int, int) -> float2 { return gv[i][r]; };
-    auto store = [&](int j, int c, float2 v) {
-      outB[base + (O)j * es + c] = grad_minus_i(op, 0, j, iz, 2, v);
+    auto store = [&](int j, int, float2 v, int i, int r) {
+      *io.last(outB, i, r) = grad_minus_i(op, 0, j, iz, 2, v);
     };
-    GStages<N, +1, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load, store);
+    GStages<N, +1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
   }
 }
 
@@ -766,8 +795,7 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
               float2* __restrict__ o0, float2* __restrict__ o1, int64_t elemStride,
               const float2* __restrict__ tw_g, KOp op) {
   constexpr int B = LptXCfg<N>::B, E = LptXCfg<N>::E, T = LptXCfg<N>::T;
-  constexpr int R0 = kFirstRadix<Plan<N>, E>, NB0 = E / R0;
-  static_assert(T % B == 0, "a thread's butterflies must share one column");
+  constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
   __shared__ float2 lds[N * B];
   __shared__ float2 tw[N];
   const int tid = threadIdx.x;
@@ -781,6 +809,7 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
   const int ny = iy < h ? iy : iy - n;
   const int n2yz = ny * ny + iz * iz;
   const float ms = -op.scale;
+  const ColTile<N, B, E, O> io(base, es, tid);
   float2 g[NB0][R0];
 #pragma unroll
   for (int i = 0; i < NB0; ++i) {
@@ -788,8 +817,7 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
       const int jj = j + r * (N / R0);
-      const O idx = base + (O)jj * es + c0;
-      const float2 a = load_stream(phi1 + idx), b = load_stream(phi2 + idx);
+      const float2 a = load_stream(io.first(phi1, i, r)), b = load_stream(io.first(phi2, i, r));
       const int nx = jj < h ? jj : jj - n;
       const int n2 = nx * nx + n2yz;
       g[i][r] = make_float2(0.f, 0.f);
@@ -805,8 +833,8 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
     auto load = [&](int i, int r, int jj, int) -> float2 {
       return t == 0 ? grad_minus_i(op, jj, iy, iz, 0, g[i][r]) : g[i][r];
     };
-    auto store = [&](int j, int c, float2 v) { store_stream(out + base + (O)j * es + c, v); };
-    GStages<N, +1, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load, store);
+    auto store = [&](int, int, float2 v, int i, int r) { store_stream(io.last(out, i, r), v); };
+    GStages<N, +1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();   // the second transform reuses the LDS tile
   }
 }
@@ -1173,7 +1201,7 @@ k_fft_screen_row(float2* __restrict__ data, const float* __restrict__ rho, float
   // latency hides behind the inverse transform.
   using RP = RowPlan<NC>;
   constexpr int RL = kLastRadix<RP, E>, NBL = E / RL;
-  constexpr bool handOff = RL == kFirstRadix<RP, E>;
+  constexpr bool handOff = RL == RP::rad[0];
   // Persistent: the work-group takes row blocks blockIdx.x, + gridDim.x, ...; the field
   // and density rows of the next block are loaded into registers while this block is
   // transformed and stored.
