@@ -238,7 +238,8 @@ static void pm_core(const cola_params& p, const Bufs& b, const float* disp, doub
   op.scale = invM;
   if (sc.screen && sc.gradient) {
     // gradient screening (k-Mouflage, App. B): the Newtonian force mesh gives
-    // |grad Phi_N|; the density is deposited again (bitwise the same) and the row kernel
+    // |grad Phi_N|; the density is deposited again (bitwise the same) from the sorted records,
+    // which this model keeps outside the mesh slots, and the row kernel
     // forms (rho - 1)(cn + c5 eps); the massless fifth force then shares 1/k^2
     KOp nop = base;
     nop.g_n = sc.cn;
@@ -246,7 +247,7 @@ static void pm_core(const cola_params& p, const Bufs& b, const float* disp, doub
     nop.step_newton = 1;
     float2* const w0[3] = {M[0], M[1], M[2]};
     fft_c2r_force3(pl, nop, nullptr, M[1], w0, b.force, s);
-    launch_deposit(L, disp, R(M[0]), b.bins, b.entries, M[1], s);
+    launch_deposit_tiles(L, R(M[0]), b.bins, b.entries, s);
     KmArgs ka;
     ka.km_r = sc.km_r;
     ka.k0 = (float)p.km_k0;

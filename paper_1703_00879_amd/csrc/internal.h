@@ -354,6 +354,9 @@ void launch_kmouflage_source(const Layout& L, const float* rho, const float* f3,
 // mesh slot (4 bytes per particle, in whole bricks of 256).
 void launch_deposit(const Layout& L, const float* disp, float* rho_padded, void* bins,
                     void* entries, void* ranks, hipStream_t s);
+// The deposit alone, from the sorted records that launch_deposit left in `bins` and `entries`.
+void launch_deposit_tiles(const Layout& L, float* rho_padded, const void* bins, const void* entries,
+                          hipStream_t s);
 size_t bins_bytes(int64_t ntiles);
 struct GatherArgs {
   const float* F3;            // interleaved force mesh (F_x, F_y, F_z) per cell
