@@ -496,10 +496,14 @@ cola_status cola_make_ic(const cola_params* p, cola_state* st, hipStream_t s) {
     KOp base;
     base.kf = (float)(2.0 * M_PI / p->box);
     // white noise -> W_k -> phi1_k = delta_k / k^2
-    launch_noise(*p, L.np, L.pitch_p, L.plane_p, R(M[0]), nullptr, s);
-    fft_r2c(pp, R(M[0]), M[0], s);
+    launch_noise(*p, L.np, L.pitch_p, L.plane_p, R(M[0]), nullptr, s, R(M[2]), b.ref);
+    fft_r2c_zy(pp, R(M[0]), M[0], s);
     float2* phi1 = L.kdep ? b.phi1 : M[1];
-    launch_ic_phi1(*p, L, M[0], phi1, b.ref, s);
+    {
+      KOp op = base;
+      op.amp = R(M[2]);
+      fft_x_op(pp, K_AMP, op, M[0], phi1, s);
+    }
     // 2LPT source S = sum_{i<j} phi_ii phi_jj - phi_ij^2 (eq. lcdm2lpt)
     for (int c = 0; c < 3; ++c) {
       KOp op = base;
@@ -511,39 +515,34 @@ cola_status cola_make_ic(const cola_params* p, cola_state* st, hipStream_t s) {
     const size_t nreal = 2 * L.pgrid_elems;
     launch_2lpt_diag(R(M[2]), R(M[3]), R(M[4]), nreal, s);
     const int mix[3][2] = {{0, 1}, {0, 2}, {1, 2}};
-    for (auto& ij : mix) {
+    float2* const off[3] = {M[0], M[3], M[4]};
+    for (int c = 0; c < 3; ++c) {
       KOp op = base;
       op.a = phi1;
-      op.comp = ij[0];
-      op.comp2 = ij[1];
+      op.comp = mix[c][0];
+      op.comp2 = mix[c][1];
       op.scale = invN;
-      fft_c2r(pp, K_HESS, op, M[0], R(M[0]), s);
-      launch_2lpt_sub(R(M[2]), R(M[0]), nreal, s);
+      fft_c2r(pp, K_HESS, op, off[c], R(off[c]), s);
     }
-    fft_r2c(pp, R(M[2]), M[2], s);
+    launch_2lpt_sub(R(M[2]), R(off[0]), R(off[1]), R(off[2]), nreal, s);
+    fft_r2c_zy(pp, R(M[2]), M[2], s);
     float2* phi2 = L.kdep ? b.phi2 : M[3];
     {
       KOp op = base;
-      op.a = M[2];
       op.g_n = -1.f;
-      op.scale = 1.f;
-      op.n = L.np;
-      op.pitch = L.pitch_p;
-      op.plane = L.plane_p;
-      launch_kspace(K_POT, op, phi2, s);   // phi2_k = -S_k / k^2
+      fft_x_op(pp, K_POT, op, M[2], phi2, s);   // phi2_k = -S_k / k^2
     }
     float2* outs[3] = {M[0], M[2], M[4]};
     const float* f3[3] = {R(M[0]), R(M[2]), R(M[4])};
     if (L.kdep) {
       // u(a_ini) = IDFT[i k (D1(k, a_0) phi1_k + D2(k, a_0) phi2_k)]
+      float2* coef = at<float2>(st->tables, L.off_lpt_coef);
+      launch_lpt_coef_ini(L, b.growth, coef, s);
       for (int c = 0; c < 3; ++c) {
         KOp op = base;
         op.a = phi1;
         op.b = phi2;
-        op.table = b.growth;
-        op.tab_slice0 = 0;
-        op.lpt_mode = 2;
-        op.kdep = 1;
+        op.coef = coef;
         op.comp = c;
         op.scale = invN;
         fft_c2r(pp, K_LPT, op, outs[c], R(outs[c]), s);

@@ -471,6 +471,13 @@ struct ColTile {
   __device__ __forceinline__ V* last(V* p, int i, int r) const { return at(p, i * (T / B) + r * (N / RL)); }
 };
 
+// |nu|^2 of the mode (ix, iy, iz).
+template <int N>
+__device__ __forceinline__ int mode_n2(int ix, int iy, int iz) {
+  const int nx = ix < N / 2 ? ix : ix - N, ny = iy < N / 2 ? iy : iy - N;
+  return nx * nx + ny * ny + iz * iz;
+}
+
 template <int N, int DIR, int KIND, int BB = ColCfg<N>::B>
 __global__ void __launch_bounds__(N * BB / ColCfg<N>::E)
 k_fft_col(float2* __restrict__ data, int64_t elemStride, int64_t tilesPerBlock,
@@ -486,20 +493,72 @@ k_fft_col(float2* __restrict__ data, int64_t elemStride, int64_t tilesPerBlock,
   const O colInBlock = (O)(tile % tpb) * B;
   const O base = (O)(tile / tpb) * (O)blockStride + colInBlock;
   const O es = (O)elemStride;
-  const float2* src = (KIND == K_COPY && op.a) ? op.a : data;
+  const float2* src = op.a ? op.a : data;
   static_assert(T % B == 0, "a thread's butterflies must share one column");
   // X pass of an inverse transform: element j is nu_x; the thread's (y, z) column
   const int col = (int)colInBlock + tid % B;
   const int iy = KIND == K_COPY ? 0 : col / op.pitch, iz = KIND == K_COPY ? 0 : col % op.pitch;
-  auto load = [&](int, int, int j, int c) -> float2 {
-    const O idx = base + (O)j * es + c;
-    if constexpr (KIND == K_COPY)
-      return src[idx];
-    else
-      return kspace_eval<KIND>(op, j, iy, iz, idx);
-  };
-  auto store = [&](int j, int c, float2 v) { data[base + (O)j * es + c] = v; };
-  GStages<N, DIR, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load, store);
+  if constexpr (KIND == K_COPY) {
+    auto load = [&](int, int, int j, int c) -> float2 { return src[base + (O)j * es + c]; };
+    auto store = [&](int j, int c, float2 v) { data[base + (O)j * es + c] = v; };
+    GStages<N, DIR, E, B, B, 1, 0, 1>::run(lds, tid, T, tw, load, store);
+  } else if constexpr (DIR > 0) {
+    // the operator is applied on the way in.  All operands are loaded before the first is
+    // used: the operator's tests, one load behind another, had the thread wait for each
+    // (second derivatives of 384^3: 174 -> 98 us; initial LPT terms,
+    // whose FP64 growth factors were read per mode too, 342 -> 239)
+    constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
+    const ColTile<N, B, E, O> io(base, es, tid);
+    float2 a[NB0][R0], b[NB0][R0];
+#pragma unroll
+    for (int i = 0; i < NB0; ++i)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) {
+        a[i][r] = *io.first(src, i, r);
+        if constexpr (KIND == K_LPT) b[i][r] = *io.first(op.b, i, r);
+      }
+    if constexpr (KIND == K_LPT) {
+      float2 cf[NB0][R0];
+#pragma unroll
+      for (int i = 0; i < NB0; ++i)
+#pragma unroll
+        for (int r = 0; r < R0; ++r)
+          cf[i][r] = op.coef[iz <= N / 2 ? mode_n2<N>((tid + i * T) / B + r * (N / R0), iy, iz) : 0];
+      auto load = [&](int i, int r, int j, int) -> float2 {
+        return lpt_apply(op, j, iy, iz, a[i][r], b[i][r], cf[i][r]);
+      };
+      auto store = [&](int, int, float2 v, int i, int r) { *io.last(data, i, r) = v; };
+      GStages<N, DIR, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
+    } else {
+      auto load = [&](int i, int r, int j, int) -> float2 {
+        return kspace_apply<KIND>(op, j, iy, iz, a[i][r]);
+      };
+      auto store = [&](int, int, float2 v, int i, int r) { *io.last(data, i, r) = v; };
+      GStages<N, DIR, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
+    }
+  } else {
+    // and on the way out, instead of by a pass of its own over the field (384^3: the potential
+    // 74 + 110 -> 96 us, the amplitudes 74 + 253 -> 187,
+    // mostly the scattered reads of their table)
+    constexpr int RL = kLastRadix<Plan<N>, E>, NBL = E / RL;
+    const ColTile<N, B, E, O> io(base, es, tid);
+    float amp[NBL][RL];
+    if constexpr (KIND == K_AMP) {
+#pragma unroll
+      for (int i = 0; i < NBL; ++i)
+#pragma unroll
+        for (int r = 0; r < RL; ++r)
+          amp[i][r] = op.amp[iz <= N / 2 ? mode_n2<N>((tid + i * T) / B + r * (N / RL), iy, iz) : 0];
+    }
+    auto load = [&](int i, int r, int, int) -> float2 { return *io.first(src, i, r); };
+    auto store = [&](int j, int, float2 v, int i, int r) {
+      if constexpr (KIND == K_AMP)
+        *io.last(data, i, r) = iz <= N / 2 ? make_float2(amp[i][r] * v.x, amp[i][r] * v.y) : make_float2(0.f, 0.f);
+      else
+        *io.last(data, i, r) = kspace_apply<KIND>(op, j, iy, iz, v);
+    };
+    GStages<N, DIR, E, B, B, 1, 0, 1, kStoreIR | kPin>::run(lds, tid, T, tw, load, store);
+  }
 }
 
 // Forward X pass that bins the power of its modes into shells instead of writing them: the
@@ -631,7 +690,7 @@ k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t el
     float2 hv[NB0][R0];
     auto store = [&](int j, int, float2 v, int i, int r) {
       if (KEEP) *io.last(data, i, r) = v;
-      hv[i][r] = kspace_apply<KIND>(op, j, iy, iz, v, v);
+      hv[i][r] = kspace_apply<KIND>(op, j, iy, iz, v);
     };
     GStages<N, -1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();   // every thread has read its last operands out of the tile
@@ -640,7 +699,7 @@ k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t el
   } else {
     auto store = [&](int j, int c, float2 v, int i, int r) {
       if (KEEP) *io.last(data, i, r) = v;
-      lds[j * B + c] = kspace_apply<KIND>(op, j, iy, iz, v, v);
+      lds[j * B + c] = kspace_apply<KIND>(op, j, iy, iz, v);
     };
     GStages<N, -1, E, B, B, 1, 0, 1, kLastToLds | kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();
@@ -1438,7 +1497,7 @@ static void autotune_impl(const FFTPlan& pl, float2* data, hipStream_t s, int ou
 }
 
 template <int N>
-static void r2c_impl(const FFTPlan& pl, const float* in, float2* out, bool x_pass, hipStream_t s) {
+static void r2c_zy_impl(const FFTPlan& pl, const float* in, float2* out, hipStream_t s) {
   const int n = pl.n, P = pl.pitch;
   const int64_t rows = (int64_t)n * n;
   {
@@ -1455,11 +1514,24 @@ static void r2c_impl(const FFTPlan& pl, const float* in, float2* out, bool x_pas
   KOp op;
   // Y pass: per x-plane, tiles of B z-columns, element stride = pitch
   y_pass<N, -1>(out, pl, op, s, "fft_y_fwd");
+}
+
+template <int N>
+static void x_op_impl(const FFTPlan& pl, int kind, const KOp& op_in, const float2* src, float2* out,
+                      hipStream_t s) {
+  KOp op = op_in;
+  op.a = src;
+  op.n = pl.n;
+  op.pitch = pl.pitch;
+  op.plane = pl.plane;
   // X pass: tiles of XCfg B (y, z) columns, element stride = plane
   constexpr int BX = XCfg<N>::B;
-  if (x_pass)
-    col_pass<N, -1, K_COPY, BX>(out, pl.plane, (int64_t)n * P / BX, (int64_t)n * P / BX, 0, pl.tw,
-                                op, s, "fft_x_fwd");
+  const int64_t tiles = (int64_t)pl.n * pl.pitch / BX;
+  switch (kind) {
+    case K_AMP: col_pass<N, -1, K_AMP, BX>(out, pl.plane, tiles, tiles, 0, pl.tw, op, s, "fft_x_fwd_amp"); break;
+    case K_POT: col_pass<N, -1, K_POT, BX>(out, pl.plane, tiles, tiles, 0, pl.tw, op, s, "fft_x_fwd_phi2"); break;
+    default: throw Error{COLA_E_ARG, "unknown k-space operator"};
+  }
 }
 
 template <int N>
@@ -1475,10 +1547,6 @@ static void c2r_impl(const FFTPlan& pl, int kind, const KOp& op_in, float2* data
   const int64_t xtiles = (int64_t)n * P / BX;
   const int64_t ES = pl.plane;
   switch (kind) {
-    case K_COPY: col_pass<N, 1, K_COPY, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv"); break;
-    case K_FORCE: col_pass<N, 1, K_FORCE, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv_force"); break;
-    case K_POT: col_pass<N, 1, K_POT, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv_pot"); break;
-    case K_SMOOTH: col_pass<N, 1, K_SMOOTH, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv_smooth"); break;
     case K_LPT: col_pass<N, 1, K_LPT, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv_lpt"); break;
     case K_HESS: col_pass<N, 1, K_HESS, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv_hess"); break;
     case K_GRAD: col_pass<N, 1, K_GRAD, BX>(data, ES, xtiles, xtiles, 0, pl.tw, op, s, "fft_x_inv_grad"); break;
@@ -1501,9 +1569,9 @@ static void c2r_impl(const FFTPlan& pl, int kind, const KOp& op_in, float2* data
   }
 }
 
-static void r2c_dispatch(const FFTPlan& pl, const float* in, float2* out, bool x_pass, hipStream_t s) {
+void fft_r2c_zy(const FFTPlan& pl, const float* in, float2* out, hipStream_t s) {
   switch (pl.n) {
-#define CASE(N_) case N_: r2c_impl<N_>(pl, in, out, x_pass, s); return;
+#define CASE(N_) case N_: r2c_zy_impl<N_>(pl, in, out, s); return;
     CASE(8) CASE(12) CASE(16) CASE(24) CASE(32) CASE(48) CASE(64) CASE(96) CASE(128)
     CASE(192) CASE(256) CASE(384) CASE(512) CASE(768) CASE(1024) CASE(1536) CASE(2048)
 #undef CASE
@@ -1511,12 +1579,14 @@ static void r2c_dispatch(const FFTPlan& pl, const float* in, float2* out, bool x
   }
 }
 
-void fft_r2c(const FFTPlan& pl, const float* in, float2* out, hipStream_t s) {
-  r2c_dispatch(pl, in, out, true, s);
-}
-
-void fft_r2c_zy(const FFTPlan& pl, const float* in, float2* out, hipStream_t s) {
-  r2c_dispatch(pl, in, out, false, s);
+void fft_x_op(const FFTPlan& pl, int kind, const KOp& op, const float2* src, float2* out, hipStream_t s) {
+  switch (pl.n) {
+#define CASE(N_) case N_: x_op_impl<N_>(pl, kind, op, src, out, s); return;
+    CASE(8) CASE(12) CASE(16) CASE(24) CASE(32) CASE(48) CASE(64) CASE(96) CASE(128)
+    CASE(192) CASE(256) CASE(384) CASE(512) CASE(768) CASE(1024) CASE(1536) CASE(2048)
+#undef CASE
+    default: throw Error{COLA_E_UNSUPPORTED, "FFT size not supported"};
+  }
 }
 
 template <int N>

@@ -845,6 +845,19 @@ void launch_lpt_coef(const Layout& L, const double* table, int64_t slice0, int64
   COLA_LAUNCH_CHECK();
 }
 
+__global__ void k_lpt_coef_ini(const double* __restrict__ table, int64_t n_k, float2* __restrict__ coef) {
+  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n_k;
+       k += (int64_t)gridDim.x * blockDim.x)
+    coef[k] = make_float2((float)table[6 * k], (float)table[6 * k + 3]);
+}
+
+void launch_lpt_coef_ini(const Layout& L, const double* table, float2* coef, hipStream_t s) {
+  ProfScope ps("lpt_coef", s);
+  const unsigned g = (unsigned)std::min<int64_t>((L.n_k + 255) / 256, 4096);
+  hipLaunchKernelGGL(k_lpt_coef_ini, dim3(g), dim3(256), 0, s, table, L.n_k, coef);
+  COLA_LAUNCH_CHECK();
+}
+
 // ------------------------------------------------------------------ triangle growth
 // Exact second-order growth of a Fourier triangle k = k1 + k2 (Sec. 4.2) beside the
 // approximation the path uses, D2_hat(k)(1 - cos^2 theta), for checking it (Fig. 1):
@@ -946,33 +959,7 @@ __device__ __forceinline__ float unit_open(uint64_t z) {   // ((z >> 11) + 1/2) 
   return ((float)(z >> 11) + 0.5f) * 0x1p-53f;
 }
 
-__global__ void k_noise(uint64_t seed, int n, int rpitch, int64_t rplane, float* __restrict__ padded,
-                        float* __restrict__ flat) {
-  const int64_t total = (int64_t)n * n * n;
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < total;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    const float u0 = unit_open(splitmix64(seed, 2 * (uint64_t)j));
-    const float u1 = unit_open(splitmix64(seed, 2 * (uint64_t)j + 1));
-    const float g = sqrtf(-2.f * logf(u0)) * cospif(2.f * u1);
-    if (padded) {
-      const int64_t r = j / n;
-      padded[(r / n) * rplane + (r % n) * rpitch + (j - r * n)] = g;
-    }
-    if (flat) flat[j] = g;
-  }
-}
-
-void launch_noise(const cola_params& p, int n, int pitch, int64_t plane, float* padded, float* flat,
-                  hipStream_t s) {
-  ProfScope ps("noise", s);
-  const int64_t total = (int64_t)n * n * n;
-  const unsigned g = (unsigned)std::min<int64_t>((total + 255) / 256, 1 << 20);
-  hipLaunchKernelGGL(k_noise, dim3(g), dim3(256), 0, s, p.seed, n, 2 * pitch, 2 * plane, padded,
-                     flat);
-  COLA_LAUNCH_CHECK();
-}
-
-// ------------------------------------------------------------------ delta_k -> phi1_k
+// ------------------------------------------------------------------ initial amplitudes
 struct EHDev {
   float ns, th2, omh, alpha, kfac;   // see SpecDev
 };
@@ -987,47 +974,65 @@ __device__ __forceinline__ float eh_T(const EHDev& e, float k) {
   return L0 / (L0 + C0 * q * q);
 }
 
-// phi1_k = W_k sqrt(N P_ini(k) / L^3) / k^2 ; zero at k = 0 and in row padding
-__global__ void k_ic_phi1(const float2* __restrict__ wk, float2* __restrict__ phi1, int n, int pitch,
-                          int64_t plane, float kf, float norm, EHDev eh,
-                          const double* __restrict__ ref) {
-  const float d1 = (float)ref[0], A = (float)ref[6];   // sigma8 normalisation of k^ns T^2
-  const float inv_d1sq = 1.f / (d1 * d1);
-  const int h = n / 2;
-  const int64_t total = (int64_t)n * n * pitch;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int iz = (int)(e % pitch);
-    const int64_t r = e / pitch;
-    const int iy = (int)(r % n), ix = (int)(r / n);
-    const int nx = ix < h ? ix : ix - n, ny = iy < h ? iy : iy - n;
-    const int n2 = nx * nx + ny * ny + iz * iz;
-    const int64_t idx = ix * plane + (int64_t)iy * pitch + iz;
-    float2 out = make_float2(0.f, 0.f);
-    if (iz <= h && n2 > 0) {
-      const float k2 = kf * kf * (float)n2;
+// What turns the white noise into phi1: phi1_k = amp[|nu|^2] W_k, amp = sqrt(N P_ini(k) / L^3) / k^2
+// and 0 at k = 0.  One entry per |nu|^2, a 128th or less of the modes.
+struct AmpTable {
+  float* amp;
+  int n;
+  float kf, norm;
+  EHDev eh;
+  const double* ref;
+};
+
+// White noise, four cells of a row a thread; the blocks past the last x-plane fill the table of
+// amplitudes, which saves a launch.  Bound by the hashes and the logarithm: 384^3 167 us, before
+// (one cell and two 64-bit divisions a thread) 253.
+__global__ void __launch_bounds__(256)
+k_noise(uint64_t seed, int n, int rpitch, int64_t rplane, float* __restrict__ padded,
+        float* __restrict__ flat, AmpTable t) {
+  if (blockIdx.y == (unsigned)n) {
+    const float d1 = (float)t.ref[0], A = (float)t.ref[6];   // sigma8 normalisation of k^ns T^2
+    const float inv_d1sq = 1.f / (d1 * d1);
+    for (int n2 = blockIdx.x * blockDim.x + threadIdx.x; n2 < t.n; n2 += gridDim.x * blockDim.x) {
+      const float k2 = t.kf * t.kf * (float)n2;
       const float k = sqrtf(k2);
-      const float T = eh_T(eh, k);
-      const float P = A * powf(k, eh.ns) * T * T * inv_d1sq;
-      const float amp = sqrtf(norm * P) / k2;
-      const float2 w = wk[idx];
-      out = make_float2(amp * w.x, amp * w.y);
+      const float T = eh_T(t.eh, k);
+      const float P = A * powf(k, t.eh.ns) * T * T * inv_d1sq;
+      t.amp[n2] = n2 > 0 ? sqrtf(t.norm * P) / k2 : 0.f;
     }
-    phi1[idx] = out;
+    return;
   }
+  CellQuad c;
+  if (!cell_quad(n, rpitch, rplane, c)) return;
+  quad_t g;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t j = (uint64_t)(c.e + i);
+    const float u0 = unit_open(splitmix64(seed, 2 * j));
+    const float u1 = unit_open(splitmix64(seed, 2 * j + 1));
+    g[i] = sqrtf(-2.f * logf(u0)) * cospif(2.f * u1);
+  }
+  if (padded) *reinterpret_cast<quad_t*>(padded + c.pe) = g;
+  if (flat) *reinterpret_cast<quad_t*>(flat + c.e) = g;
 }
 
-void launch_ic_phi1(const cola_params& p, const Layout& L, const float2* wk, float2* phi1,
-                    const double* ref, hipStream_t s) {
-  ProfScope ps("ic_phi1", s);
-  const SpecDev d = spec_dev(p);
-  const EHDev e{(float)d.ns, (float)d.th2, (float)d.omh, (float)d.alpha, (float)d.kfac};
-  const double N = (double)L.N;
-  const float norm = (float)(N / (p.box * p.box * p.box));
-  const int64_t total = (int64_t)L.np * L.np * L.pitch_p;
-  const unsigned g = (unsigned)std::min<int64_t>((total + 255) / 256, 1 << 20);
-  hipLaunchKernelGGL(k_ic_phi1, dim3(g), dim3(256), 0, s, wk, phi1, L.np, L.pitch_p, L.plane_p,
-                     (float)(2.0 * M_PI / p.box), norm, e, ref);
+void launch_noise(const cola_params& p, int n, int pitch, int64_t plane, float* padded, float* flat,
+                  hipStream_t s, float* amp, const double* ref) {
+  ProfScope ps("noise", s);
+  dim3 grid = quad_grid(n);
+  AmpTable t{};
+  if (amp) {
+    const SpecDev d = spec_dev(p);
+    const double N = (double)n * n * n;
+    t.amp = amp;
+    t.n = 3 * (n / 2) * (n / 2) + 1;
+    t.kf = (float)(2.0 * M_PI / p.box);
+    t.norm = (float)(N / (p.box * p.box * p.box));
+    t.eh = EHDev{(float)d.ns, (float)d.th2, (float)d.omh, (float)d.alpha, (float)d.kfac};
+    t.ref = ref;
+    grid.y += 1;
+  }
+  hipLaunchKernelGGL(k_noise, grid, dim3(256), 0, s, p.seed, n, 2 * pitch, 2 * plane, padded, flat, t);
   COLA_LAUNCH_CHECK();
 }
 

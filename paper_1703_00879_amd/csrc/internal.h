@@ -45,6 +45,26 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nblocks) {
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + l;
 }
 
+// ------------------------------------------------------------------ cells by fours
+// Four neighbouring cells of an x-plane (blockIdx.y): e, where they start in an unpadded mesh,
+// and pe, in a mesh of padded rows.  Rows are a multiple of four cells and planes have fewer
+// than 2^32, so a thread needs one 32-bit division where each cell needed two of 64 bits.
+struct CellQuad {
+  int64_t e, pe;
+};
+__device__ __forceinline__ bool cell_quad(int n, int rpitch, int64_t rplane, CellQuad& c) {
+  const unsigned q = blockIdx.x * blockDim.x + threadIdx.x, nq = (unsigned)n / 4;
+  if (q >= nq * (unsigned)n) return false;
+  const unsigned row = q / nq, z = 4 * (q - row * nq);
+  c.e = ((int64_t)blockIdx.y * n + row) * n + z;
+  c.pe = blockIdx.y * rplane + (int64_t)row * rpitch + z;
+  return true;
+}
+inline dim3 quad_grid(int n) { return dim3((unsigned)(((int64_t)n * (n / 4) + 255) / 256), (unsigned)n); }
+
+// four floats at any 4-byte aligned address (a caller's mesh need not start on 16 bytes)
+typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
+
 // ------------------------------------------------------------------ layout
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
@@ -197,23 +217,20 @@ __device__ __forceinline__ const StepDev& step_entry(const StepDev* steps, const
 
 // ------------------------------------------------------------------ k-space operators
 enum KKind : int {
-  K_COPY = 0,      // out = scale * a
-  K_FORCE = 1,     // out = -i k_c [g_n/k^2 a + g_5/(k^2+a2m2) b] * scale
+  K_COPY = 0,      // out = a
   K_POT = 2,       // out = g_n/k^2 a * scale
   K_SMOOTH = 3,    // out = W(kR) a * scale (k = 0 -> 0)
-  K_LPT = 4,       // out = i k_c (X1 a + X2 b) * scale, X from the growth table
+  K_LPT = 4,       // out = i k_c (X1 a + X2 b) * scale, (X1, X2) = coef[|nu|^2]
   K_HESS = 5,      // out = -k_i k_j a * scale
   K_GRAD = 6,      // out = i k_c a * scale
-  K_INVLAP = 7,    // out = g_n/k^2 a * scale (alias of K_POT with separate name)
+  K_AMP = 7,       // out = amp[|nu|^2] a
 };
 
 struct KOp {
   const float2* a = nullptr;
   const float2* b = nullptr;
-  const double* table = nullptr;   // growth table base (K_LPT)
-  int64_t tab_slice0 = 0, tab_slice1 = 0;   // element offsets of two slices (K_LPT)
-  int lpt_mode = 0;                // 0: X = D''(slice0); 1: X = D(slice1) - D(slice0); 2: X = D(slice0)
-  const float2* coef = nullptr;    // K_LPT: the step's (X1, X2) per |nu|^2 in FP32, if built
+  const float2* coef = nullptr;    // K_LPT: (X1, X2) per |nu|^2 in FP32
+  const float* amp = nullptr;      // K_AMP: a factor per |nu|^2, zero at the first
   // when set, the step-dependent coefficients (g_n, g_5, a2m2) come from step_entry();
   // with step_newton the force pass takes the Newtonian part alone (g_n = the step's cn)
   const StepDev* steps = nullptr;
@@ -227,7 +244,6 @@ struct KOp {
   int filter = 0;
   int n = 0, pitch = 0;
   int64_t plane = 0;
-  int kdep = 0;                    // growth table indexed by |nu|^2 (else entry 0)
 };
 
 // ------------------------------------------------------------------ FFT
@@ -238,10 +254,11 @@ struct FFTPlan {
   const float2* tw = nullptr;   // exp(-2 pi i t / n), t = 0..n-1 (device)
 };
 bool fft_size_supported(int n);
-// forward real-to-complex 3D transform (unnormalised, e^{-ikx}); in may alias out
-void fft_r2c(const FFTPlan& pl, const float* in, float2* out, hipStream_t s);
-// its Z and Y passes only: the X pass is left to fft_screen / fft_c2r_force3
+// Z and Y passes of the forward real-to-complex 3D transform (unnormalised, e^{-ikx}); in may
+// alias out.  The X pass is left to fft_x_op / fft_screen / fft_c2r_force3 / fft_x_pk.
 void fft_r2c_zy(const FFTPlan& pl, const float* in, float2* out, hipStream_t s);
+// Forward X pass of `src` through the operator (K_AMP or K_POT) into `out` (may alias src).
+void fft_x_op(const FFTPlan& pl, int kind, const KOp& op, const float2* src, float2* out, hipStream_t s);
 // inverse complex-to-real 3D transform (unnormalised, e^{+ikx}).  The first pass reads
 // through the k-space operator `op` (kind) and writes `data`; later passes are in place;
 // the real result goes to `out` (may alias data).
@@ -316,13 +333,12 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
 // out[i] = (exact, approximation); NaN for sets that are no triangle
 void launch_growth_triangles(const cola_params& p, int n, const double* tri, double a, double* out,
                              hipStream_t s);
+// white noise (padded or flat, or both); with amp also the table of phi1_k / W_k per |nu|^2,
+// 3 (n/2)^2 + 1 entries, from ref (see launch_growth_ode)
 void launch_noise(const cola_params& p, int n, int pitch, int64_t plane, float* dst_padded,
-                  float* dst_flat, hipStream_t s);
-void launch_ic_phi1(const cola_params& p, const Layout& L, const float2* wk, float2* phi1,
-                    const double* ref, hipStream_t s);
-void launch_kspace(int kind, const KOp& op, float2* out, hipStream_t s);
+                  float* dst_flat, hipStream_t s, float* amp = nullptr, const double* ref = nullptr);
 void launch_2lpt_diag(float* d0, const float* d1, const float* d2, size_t n, hipStream_t s);
-void launch_2lpt_sub(float* acc, const float* d, size_t n, hipStream_t s);
+void launch_2lpt_sub(float* acc, const float* x, const float* y, const float* z, size_t n, hipStream_t s);
 // out[c][p] = alpha * f0[c](q_p) + beta * f1[c](q_p) from padded particle-grid fields
 void launch_unpad3(const Layout& L, const float* const f0[3], const float* const f1[3],
                    float alpha, float beta, float* out, hipStream_t s);
@@ -333,6 +349,8 @@ void launch_combine_u0(const Layout& L, const float* psi1, const float* psi2,
 // D2(a_i)) (differences taken in FP64), from table slices at element offsets slice0/slice1.
 void launch_lpt_coef(const Layout& L, const double* table, int64_t slice0, int64_t slice1,
                      const StepDev* steps, const int* ctr, float2* coef, hipStream_t s);
+// the same for the initial displacement: coef[k] = (D1(a_0), D2(a_0))
+void launch_lpt_coef_ini(const Layout& L, const double* table, float2* coef, hipStream_t s);
 // the step table of a run; the step counter: *ctr = v; *ctr += 1 (single-thread kernels)
 void launch_write_steps(const cola_params& p, const Layout& L, StepDev* steps, hipStream_t s);
 void launch_set_counter(int* ctr, int v, hipStream_t s);

@@ -33,10 +33,9 @@ __device__ __forceinline__ float smooth_window(float k2R2, int filter) {
   return 3.f * (s - x * c) / (x * x * x);
 }
 
-// Value of operator KIND at mode (ix, iy, iz) given the raw source values a (and b).
+// Value of operator KIND at mode (ix, iy, iz) given the source's value a.
 template <int KIND>
-__device__ __forceinline__ float2 kspace_apply(const KOp& op, int ix, int iy, int iz, float2 a,
-                                               float2 b) {
+__device__ __forceinline__ float2 kspace_apply(const KOp& op, int ix, int iy, int iz, float2 a) {
   const int n = op.n, h = n >> 1;
   if (iz > h) return make_float2(0.f, 0.f);
   const int nx = ix < h ? ix : ix - n;
@@ -50,16 +49,7 @@ __device__ __forceinline__ float2 kspace_apply(const KOp& op, int ix, int iy, in
   const bool nyq_c = ic == h, nyq_c2 = jc == h;
   const float k_c = op.kf * (float)(op.comp == 0 ? nx : (op.comp == 1 ? ny : nz));
   const float k_c2 = op.kf * (float)(op.comp2 == 0 ? nx : (op.comp2 == 1 ? ny : nz));
-  if constexpr (KIND == K_COPY) {
-    return make_float2(op.scale * a.x, op.scale * a.y);
-  } else if constexpr (KIND == K_FORCE) {
-    if (n2 == 0 || nyq_c) return make_float2(0.f, 0.f);
-    const float k2 = op.kf * op.kf * (float)n2;
-    const float gn = op.g_n * fast_rcp(k2), g5 = op.g_5 * fast_rcp(k2 + op.a2m2);
-    const float2 g = make_float2(gn * a.x + g5 * b.x, gn * a.y + g5 * b.y);
-    const float f = k_c * op.scale;   // -i k_c g
-    return make_float2(f * g.y, -f * g.x);
-  } else if constexpr (KIND == K_POT) {
+  if constexpr (KIND == K_POT) {
     if (n2 == 0) return make_float2(0.f, 0.f);
     const float k2 = op.kf * op.kf * (float)n2;
     const float f = op.g_n * fast_rcp(k2) * op.scale;
@@ -69,29 +59,6 @@ __device__ __forceinline__ float2 kspace_apply(const KOp& op, int ix, int iy, in
     const float k2 = op.kf * op.kf * (float)n2;
     const float f = smooth_window(k2 * op.r_smooth * op.r_smooth, op.filter) * op.scale;
     return make_float2(f * a.x, f * a.y);
-  } else if constexpr (KIND == K_LPT) {
-    if (n2 == 0 || nyq_c) return make_float2(0.f, 0.f);
-    float x1, x2;
-    const int64_t e = (int64_t)(op.kdep ? n2 : 0) * 6;
-    const double* t0 = op.table + op.tab_slice0 + e;
-    const double* t1 = op.table + op.tab_slice1 + e;
-    if (op.coef) {                   // the step's FP32 pairs: one 8-byte read per mode
-      const float2 cf = op.coef[op.kdep ? n2 : 0];
-      x1 = cf.x;
-      x2 = cf.y;
-    } else if (op.lpt_mode == 0) {   // second derivatives at slice 0
-      x1 = (float)t0[2];
-      x2 = (float)t0[5];
-    } else if (op.lpt_mode == 1) {   // D(slice 1) - D(slice 0)
-      x1 = (float)(t1[0] - t0[0]);
-      x2 = (float)(t1[3] - t0[3]);
-    } else {                         // D(slice 0)
-      x1 = (float)t0[0];
-      x2 = (float)t0[3];
-    }
-    const float2 g = make_float2(x1 * a.x + x2 * b.x, x1 * a.y + x2 * b.y);
-    const float f = k_c * op.scale;   // +i k_c g
-    return make_float2(-f * g.y, f * g.x);
   } else if constexpr (KIND == K_HESS) {
     if (op.comp != op.comp2 && (nyq_c || nyq_c2)) return make_float2(0.f, 0.f);
     const float f = -k_c * k_c2 * op.scale;
@@ -105,17 +72,18 @@ __device__ __forceinline__ float2 kspace_apply(const KOp& op, int ix, int iy, in
   }
 }
 
-// Sources an operator reads (a always; b for K_FORCE with a screened source and K_LPT).
-template <int KIND>
-__device__ __forceinline__ bool kspace_uses_b(const KOp& op) {
-  return (KIND == K_LPT) || (KIND == K_FORCE && op.b != nullptr);
-}
-
-template <int KIND>
-__device__ __forceinline__ float2 kspace_eval(const KOp& op, int ix, int iy, int iz, int64_t idx) {
-  const float2 a = op.a[idx];
-  const float2 b = kspace_uses_b<KIND>(op) ? op.b[idx] : a;
-  return kspace_apply<KIND>(op, ix, iy, iz, a, b);
+// K_LPT at mode (ix, iy, iz): i k_c (c.x a + c.y b) scale, c the mode's FP32 growth factors.
+__device__ __forceinline__ float2 lpt_apply(const KOp& op, int ix, int iy, int iz, float2 a, float2 b,
+                                            float2 c) {
+  const int n = op.n, h = n >> 1;
+  if (iz > h) return make_float2(0.f, 0.f);
+  const int nx = ix < h ? ix : ix - n, ny = iy < h ? iy : iy - n;
+  const int ic = op.comp == 0 ? ix : (op.comp == 1 ? iy : iz);
+  if (nx * nx + ny * ny + iz * iz == 0 || ic == h) return make_float2(0.f, 0.f);
+  const float k_c = op.kf * (float)(op.comp == 0 ? nx : (op.comp == 1 ? ny : iz));
+  const float2 g = make_float2(fmaf(c.y, b.x, c.x * a.x), fmaf(c.y, b.y, c.x * a.y));
+  const float f = k_c * op.scale;   // +i k_c g
+  return make_float2(-f * g.y, f * g.x);
 }
 
 // Potential part of the force operator: [g_n/k^2 a + g_5/(k^2 + a2m2) b] * scale
