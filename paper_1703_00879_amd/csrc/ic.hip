@@ -228,7 +228,8 @@ __device__ __forceinline__ void growth_model(const GrowthDev& g, const MBSpline&
 //
 // What bounds it: up to about 10^5 modes (a wave or two per SIMD) the latency of one mode's
 // chain of steps, so few, wide steps whose four sequences advance independently.  Measured
-// on a whole table from z = 19: LCDM, 64^3 particles, 10 slices, 6.5 -> 0.24 ms, against
+// on a whole table from z = 19: LCDM, 10 slices, 6.5 -> 0.08 ms (0.24 with the divisions of
+// the mode terms, which one mode at k = 0 does not need), against
 // fourth-order Runge-Kutta steps of 1e-3 that evaluated the model in full for every mode
 // and stage.  Steps of 0.04 hold the largest relative error of any table entry at 1e-13 (the
 // Runge-Kutta steps: 4e-13, 9e-12 for the symmetron); it is truncation from 0.05 on, rounding
@@ -312,10 +313,17 @@ k_growth_nodes(GrowthDev g, MBSpline mb, GrowthSteps st, GrowthNode* __restrict_
 // One mode's coefficients at a point; HALF (the COLA_READ_D2_HALF_K reading): y also
 // carries (D1, D1') at k/sqrt2, whose q is qh, and the D2 source takes that D1 squared in
 // place of D1(k)^2.
-template <bool HALF>
+// KDEP: the table has an entry per mode; else k = 0, where the terms in R and Q vanish.
+template <bool HALF, bool KDEP>
 struct GrowthMode {
   double f, q, g, qh;
   __device__ __forceinline__ GrowthMode(const GrowthNode& n, double k2, bool ref) {
+    if constexpr (!KDEP) {
+      f = n.f;
+      q = qh = ref ? n.kap : n.A;
+      g = ref ? 0.0 : n.s;
+      return;
+    }
     const double R = 1.0 / (k2 + n.m), Q = 1.0 / (0.5 * k2 + n.m);
     f = n.f;
     q = ref ? n.kap : n.A + n.B * (k2 * R);
@@ -343,10 +351,10 @@ struct GrowthMode {
 };
 
 // one slice of the table from the state y at the point of `nd`
-template <bool HALF>
+template <bool HALF, bool KDEP>
 __device__ __forceinline__ void growth_store(const GrowthNode& nd, double k2, bool ref, const double* y,
                                              double* out) {
-  const GrowthMode<HALF> c(nd, k2, ref);
+  const GrowthMode<HALF, KDEP> c(nd, k2, ref);
   const double ds = HALF ? y[4] : y[0];
   const double tau = 1.0 / c.f;   // D'' is per tau
   out[0] = y[0];
@@ -415,7 +423,7 @@ __device__ __forceinline__ double sigma8_norm(const SpecDev& sp) {
 // by every sequence that has a substep there.  The last work-group computes the spectrum's
 // normalisation into ref_out[6] meanwhile: it is done well before the tables, and the host,
 // whose own quadrature took 4-5 ms a run, only launches.
-template <bool HALF>
+template <bool HALF, bool KDEP>
 __global__ void __launch_bounds__(64)
 k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int nsteps,
              double* __restrict__ table, double* __restrict__ ref_out) {
@@ -452,7 +460,7 @@ k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int 
       for (int e = threadIdx.x; e < ns * kGrowthNodes * V; e += blockDim.x) dst[e] = src[e];
     }
     __syncthreads();
-    if (s0 == 0 && store) growth_store<HALF>(nd[0], k2, ref, y, table + t * 6);
+    if (s0 == 0 && store) growth_store<HALF, KDEP>(nd[0], k2, ref, y, table + t * 6);
     for (int s = 0; s < ns; ++s) {
       const GrowthNode* p = nd + s * kGrowthNodes;
       const double H = p[0].ext;
@@ -463,7 +471,7 @@ k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int 
         for (int v = 0; v < NV; ++v) zm[j][v] = z[j][v] = y[v];
       // sequence j (2 j + 2 substeps) from point i to its next one; the first substep is an
       // Euler step of half the midpoint's length
-      auto sub = [&](int i, int j, const GrowthMode<HALF>& c) {
+      auto sub = [&](int i, int j, const GrowthMode<HALF, KDEP>& c) {
         const double h = H / (double)(2 * j + 2);
         c.midpoint(zm[j], z[j], i == 0 ? h : 2.0 * h);
       };
@@ -471,7 +479,7 @@ k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int 
       constexpr int who[kGrowthNodes - 1] = {15, 8, 4, 2 | 8, 4, 8, 15, 8, 4, 2 | 8, 4, 8};
 #pragma unroll
       for (int i = 0; i < kGrowthNodes - 1; ++i) {
-        const GrowthMode<HALF> c(p[i], k2, ref);
+        const GrowthMode<HALF, KDEP> c(p[i], k2, ref);
 #pragma unroll
         for (int j = 0; j < NS; ++j)
           if ((who[i] >> j) & 1) sub(i, j, c);
@@ -479,9 +487,9 @@ k_growth_ode(GrowthDev g, SpecDev sp, const GrowthNode* __restrict__ nodes, int 
 #pragma unroll
       for (int v = 0; v < NV; ++v) y[v] = (wt[0] * z[0][v] + wt[1] * z[1][v]) + (wt[2] * z[2][v] + wt[3] * z[3][v]);
       const int out = (int)p[kGrowthNodes - 1].ext;   // uniform over the work-group
-      if (out >= 0 && store) growth_store<HALF>(p[kGrowthNodes - 1], k2, ref, y, table + ((int64_t)out * g.n_k + t) * 6);
+      if (out >= 0 && store) growth_store<HALF, KDEP>(p[kGrowthNodes - 1], k2, ref, y, table + ((int64_t)out * g.n_k + t) * 6);
     }
-    if (t == g.n_k && s0 + ns == nsteps) growth_store<HALF>(nd[ns * kGrowthNodes - 1], k2, ref, y, ref_out);
+    if (t == g.n_k && s0 + ns == nsteps) growth_store<HALF, KDEP>(nd[ns * kGrowthNodes - 1], k2, ref, y, ref_out);
   }
 }
 
@@ -811,10 +819,10 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
   }
   flush();
   const dim3 grid((unsigned)((L.n_k + 1 + 63) / 64) + 1), block(64);
-  if (p.readings & COLA_READ_D2_HALF_K)
-    hipLaunchKernelGGL(k_growth_ode<true>, grid, block, 0, s, g, sp, nodes, nsteps, table, ref);
-  else
-    hipLaunchKernelGGL(k_growth_ode<false>, grid, block, 0, s, g, sp, nodes, nsteps, table, ref);
+  const bool half = (p.readings & COLA_READ_D2_HALF_K) != 0;
+  auto* kernel = half ? (g.kdep ? k_growth_ode<true, true> : k_growth_ode<true, false>)
+                      : (g.kdep ? k_growth_ode<false, true> : k_growth_ode<false, false>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, s, g, sp, nodes, nsteps, table, ref);
   COLA_LAUNCH_CHECK();
 }
 
