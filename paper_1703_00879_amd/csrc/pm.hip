@@ -331,32 +331,54 @@ k_bin_scatter(const float* __restrict__ disp, BinGeo g, const uint32_t* __restri
   }
 }
 
+// Particles of a tile, all classes.
+__device__ __forceinline__ uint32_t tile_total(const uint32_t* __restrict__ cnt, int64_t tile, uint32_t* c) {
+  const uint4* c4 = reinterpret_cast<const uint4*>(cnt + tile * 8);
+  const uint4 a = c4[0], b = c4[1];
+  c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w; c[4] = b.x; c[5] = b.y; c[6] = b.z; c[7] = b.w;
+  return c[0] + c[1] + c[2] + c[3] + c[4] + c[5] + c[6] + c[7];
+}
+
+// Sum of v over the threads before this one (exclusive scan) of a work-group of 1024 at most;
+// total: over all of them.  part: one word a wave.
+__device__ __forceinline__ uint32_t group_scan(uint32_t v, uint32_t* part, uint32_t& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  uint32_t inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += u;
+  }
+  __syncthreads();   // the words of an earlier scan have been read
+  if (lane == 63) part[wave] = inc;
+  __syncthreads();
+  uint32_t before = 0;
+  total = 0;
+  for (int w = 0; w < waves; ++w) {
+    if (w < wave) before += part[w];
+    total += part[w];
+  }
+  return before + inc - v;
+}
+
 // Tile totals -> per-block sums (block of kScanBlock tiles).
 __global__ void __launch_bounds__(256)
 k_scan_reduce(const uint32_t* __restrict__ cnt, uint32_t* __restrict__ bsum, int64_t ntiles) {
-  __shared__ uint32_t red[256];
+  __shared__ uint32_t part[16];
   const int64_t t0 = (int64_t)blockIdx.x * kScanBlock;
-  uint32_t s = 0;
+  uint32_t s = 0, c[8];
   for (int i = threadIdx.x; i < kScanBlock; i += 256) {
     const int64_t t = t0 + i;
-    if (t < ntiles) {
-      const uint4* c4 = reinterpret_cast<const uint4*>(cnt + t * 8);
-      const uint4 a = c4[0], b = c4[1];
-      s += a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
-    }
+    if (t < ntiles) s += tile_total(cnt, t, c);
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = red[0];
+  uint32_t total;
+  group_scan(s, part, total);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
 // Exclusive scan of the block sums (one work-group; nblk <= 4096 for nmesh <= 2048).
 __global__ void __launch_bounds__(1024) k_scan_top(uint32_t* __restrict__ bsum, int nblk) {
-  __shared__ uint32_t part[1024];
+  __shared__ uint32_t part[16];
   const int t = threadIdx.x;
   const int per = (nblk + 1023) / 1024;
   uint32_t s = 0;
@@ -364,15 +386,7 @@ __global__ void __launch_bounds__(1024) k_scan_top(uint32_t* __restrict__ bsum, 
     const int j = t * per + i;
     if (j < nblk) s += bsum[j];
   }
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const uint32_t v = t >= off ? part[t - off] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  uint32_t run = part[t] - s;
+  uint32_t total, run = group_scan(s, part, total);
   for (int i = 0; i < per; ++i) {
     const int j = t * per + i;
     if (j < nblk) {
@@ -383,30 +397,29 @@ __global__ void __launch_bounds__(1024) k_scan_top(uint32_t* __restrict__ bsum, 
   }
 }
 
-// Per block: scan of tile totals + block offset -> start[tile]; per-class cursors.
+// Per block: scan of tile totals + block offset -> start[tile]; per-class cursors.  Up to
+// kScanAlone blocks (boff null) a block adds up the tiles before its own itself, at most
+// 32 KB a block from the L2, and the two launches before this one are saved (192^3 cells 14.1 -> 4.6 us, 384^3 13.8 -> 8.2).
+constexpr int kScanAlone = 16;
 __global__ void __launch_bounds__(kScanBlock)
 k_scan_apply(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ boff,
              uint32_t* __restrict__ start, uint32_t* __restrict__ cur, int64_t ntiles) {
-  __shared__ uint32_t part[kScanBlock];
+  __shared__ uint32_t part[16];
   const int t = threadIdx.x;
   const int64_t tile = (int64_t)blockIdx.x * kScanBlock + t;
   uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (tile < ntiles) {
-    const uint4* c4 = reinterpret_cast<const uint4*>(cnt + tile * 8);
-    const uint4 a = c4[0], b = c4[1];
-    c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w; c[4] = b.x; c[5] = b.y; c[6] = b.z; c[7] = b.w;
+  uint32_t offset = 0, total;
+  if (boff) {
+    offset = boff[blockIdx.x];
+  } else if (blockIdx.x > 0) {
+    uint32_t s = 0;
+    for (unsigned b = 0; b < blockIdx.x; ++b) s += tile_total(cnt, (int64_t)b * kScanBlock + t, c);
+    group_scan(s, part, offset);
   }
-  const uint32_t tot = c[0] + c[1] + c[2] + c[3] + c[4] + c[5] + c[6] + c[7];
-  part[t] = tot;
-  __syncthreads();
-  for (int off = 1; off < kScanBlock; off <<= 1) {
-    const uint32_t v = t >= off ? part[t - off] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
+  const uint32_t tot = tile < ntiles ? tile_total(cnt, tile, c) : 0;
+  const uint32_t before = group_scan(tot, part, total);
   if (tile < ntiles) {
-    uint32_t run = boff[blockIdx.x] + part[t] - tot;
+    uint32_t run = offset + before;
     start[tile] = run;
     uint32_t cc[8];
 #pragma unroll
@@ -632,10 +645,13 @@ void launch_deposit(const Layout& L, const float* disp, float* rho, void* bins, 
   }
   {
     ProfScope ps("bin_scan", s);
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nblk), dim3(256), 0, s, cnt, bsum, L.ntiles);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, (int)nblk);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nblk), dim3(kScanBlock), 0, s, cnt, bsum, start,
-                       cur, L.ntiles);
+    const bool alone = nblk <= kScanAlone;
+    if (!alone) {
+      hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nblk), dim3(256), 0, s, cnt, bsum, L.ntiles);
+      hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, (int)nblk);
+    }
+    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nblk), dim3(kScanBlock), 0, s, cnt,
+                       alone ? nullptr : bsum, start, cur, L.ntiles);
     COLA_LAUNCH_CHECK();
   }
   {
