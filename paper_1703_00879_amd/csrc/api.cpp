@@ -321,12 +321,12 @@ static void step_impl(const cola_params* p, cola_state* st, int32_t i, void* wor
     const FFTPlan pp = plan_part(b);
     float2* coef = at<float2>(st->tables, L.off_lpt_coef);
     launch_lpt_coef(L, b.growth, 0, 0, steps, ctr, coef, s);
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < 2; t += L.lpt_terms) {
       KOp op;
       op.kf = (float)(2.0 * M_PI / p->box);
       op.coef = coef + (t == 0 ? 0 : L.n_k);
       op.scale = (float)(1.0 / (double)L.N);
-      fft_c2r_lpt3(pp, op, b.phi1, b.phi2, b.lptw, t == 0 ? b.lpp3 : b.dlt3, s);
+      fft_c2r_lpt3(pp, op, b.phi1, b.phi2, L.lpt_terms, L.n_k, b.lptw, t == 0 ? b.lpp3 : b.dlt3, s);
     }
     g.lpp3 = b.lpp3;
     g.dlt3 = b.dlt3;

@@ -837,7 +837,8 @@ k_fft_col_inv_yz(const float2* data, float2* outA, float2* __restrict__ outB, in
 // registers from one read of each potential, and two X transforms go out through the LDS
 // tile, as in k_fft_col_fwd_force: G0 = X^-1[-i k_x A] (= X^-1[i k_x (c1 phi1 + c2 phi2)]/N)
 // into o0 and G = X^-1[A] into o1, from which the Y passes of the force transforms give
-// the three components.  Columns past z = n/2 (row padding) get zeros.
+// the three components.  Columns past z = n/2 (row padding) get zeros.  With two terms the
+// second has its coefficients coef_stride further on and its fields behind the first's.
 template <int N>
 struct LptXCfg {
   static constexpr int B = XCfg<N>::B;
@@ -852,7 +853,7 @@ __global__ void __launch_bounds__(LptXCfg<N>::T)
 __attribute__((amdgpu_waves_per_eu(N == 1024 ? 4 : 1)))
 k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
               float2* __restrict__ o0, float2* __restrict__ o1, int64_t elemStride,
-              const float2* __restrict__ tw_g, KOp op) {
+              const float2* __restrict__ tw_g, KOp op, int terms, int64_t coef_stride) {
   constexpr int B = LptXCfg<N>::B, E = LptXCfg<N>::E, T = LptXCfg<N>::T;
   constexpr int R0 = Plan<N>::rad[0], NB0 = E / R0;
   __shared__ float2 lds[N * B];
@@ -860,7 +861,16 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += T) tw[i] = tw_g[i];   // first read after stage 0's barrier
   using O = Off<N>;
-  const O base = (O)xcd_block(blockIdx.x, gridDim.x) * B, es = (O)elemStride;
+  // the terms of a tile are neighbours, so that the second finds the potentials in the L2
+  unsigned blk = xcd_block(blockIdx.x, gridDim.x);
+  if (terms == 2) {
+    const unsigned term = blk & 1;
+    blk >>= 1;
+    op.coef += term * coef_stride;
+    o0 += (int64_t)term * N * elemStride;
+    o1 += (int64_t)term * N * elemStride;
+  }
+  const O base = (O)blk * B, es = (O)elemStride;
   const int c0 = tid % B;
   const int col = (int)base + c0;
   const int iy = col / op.pitch, iz = col % op.pitch;
@@ -1419,21 +1429,23 @@ static int y_tile(int dir) {
 }
 
 template <int N, int DIR, int B>
-static void y_pass_b(float2* data, const FFTPlan& pl, const KOp& op, hipStream_t s, const char* name) {
+static void y_pass_b(float2* data, const FFTPlan& pl, const KOp& op, hipStream_t s, const char* name,
+                     int fields) {
   if constexpr (kTileOk<N, B>) {
     const int P = pl.pitch;
-    col_pass<N, DIR, K_COPY, B>(data, P, (int64_t)pl.n * (P / B), P / B, pl.plane, pl.tw, op, s, name);
+    col_pass<N, DIR, K_COPY, B>(data, P, (int64_t)fields * pl.n * (P / B), P / B, pl.plane, pl.tw, op, s, name);
   } else {
     throw Error{COLA_E_ARG, "Y-pass tile width not valid for this size"};
   }
 }
 
 template <int N, int DIR>
-static void y_pass(float2* data, const FFTPlan& pl, const KOp& op, hipStream_t s, const char* name) {
+static void y_pass(float2* data, const FFTPlan& pl, const KOp& op, hipStream_t s, const char* name,
+                   int fields = 1) {   // fields one behind the other
   switch (y_tile<N>(DIR)) {
-    case 4: y_pass_b<N, DIR, 4>(data, pl, op, s, name); break;
-    case 8: y_pass_b<N, DIR, 8>(data, pl, op, s, name); break;
-    default: y_pass_b<N, DIR, 16>(data, pl, op, s, name); break;
+    case 4: y_pass_b<N, DIR, 4>(data, pl, op, s, name, fields); break;
+    case 8: y_pass_b<N, DIR, 8>(data, pl, op, s, name, fields); break;
+    default: y_pass_b<N, DIR, 16>(data, pl, op, s, name, fields); break;
   }
 }
 
@@ -1468,13 +1480,13 @@ static void autotune_impl(const FFTPlan& pl, float2* data, hipStream_t s, int ou
       if (!tile_valid<N>(b)) continue;
       auto run = [&] {
         if (d == 0) {
-          if (b == 4) y_pass_b<N, -1, 4>(data, pl, none, s, "fft_y_tune");
-          else if (b == 8) y_pass_b<N, -1, 8>(data, pl, none, s, "fft_y_tune");
-          else y_pass_b<N, -1, 16>(data, pl, none, s, "fft_y_tune");
+          if (b == 4) y_pass_b<N, -1, 4>(data, pl, none, s, "fft_y_tune", 1);
+          else if (b == 8) y_pass_b<N, -1, 8>(data, pl, none, s, "fft_y_tune", 1);
+          else y_pass_b<N, -1, 16>(data, pl, none, s, "fft_y_tune", 1);
         } else {
-          if (b == 4) y_pass_b<N, 1, 4>(data, pl, none, s, "fft_y_tune");
-          else if (b == 8) y_pass_b<N, 1, 8>(data, pl, none, s, "fft_y_tune");
-          else y_pass_b<N, 1, 16>(data, pl, none, s, "fft_y_tune");
+          if (b == 4) y_pass_b<N, 1, 4>(data, pl, none, s, "fft_y_tune", 1);
+          else if (b == 8) y_pass_b<N, 1, 8>(data, pl, none, s, "fft_y_tune", 1);
+          else y_pass_b<N, 1, 16>(data, pl, none, s, "fft_y_tune", 1);
         }
       };
       run();   // warm-up
@@ -1627,13 +1639,13 @@ void fft_c2r(const FFTPlan& pl, int kind, const KOp& op, float2* data, float* ou
 // interleaved rows out3[((x n + y) n + z) 3 + c].
 template <int N>
 static void grad3_tail(const FFTPlan& pl, const KOp& op, float2* const work[3], float* out3,
-                       bool lpt, hipStream_t s) {
+                       bool lpt, hipStream_t s, int fields = 1) {
   const int n = pl.n, P = pl.pitch;
-  const int64_t rows = (int64_t)n * n;
+  const int64_t rows = (int64_t)fields * n * n;
   constexpr int B = ColCfg<N>::B;
   KOp none;
-  const int64_t ytiles = (int64_t)n * (P / B);
-  y_pass<N, 1>(work[0], pl, none, s, lpt ? "lpt_fft_y_inv" : "fft_y_inv");
+  const int64_t ytiles = (int64_t)fields * n * (P / B);
+  y_pass<N, 1>(work[0], pl, none, s, lpt ? "lpt_fft_y_inv" : "fft_y_inv", fields);
   {
     ProfScope ps(lpt ? "lpt_fft_y_inv_yz" : "fft_y_inv_yz", s);
     hipLaunchKernelGGL((k_fft_col_inv_yz<N>), dim3((unsigned)ytiles), dim3(FusedCfg<N, B>::T), 0, s,
@@ -1680,7 +1692,8 @@ static void force3_impl(const FFTPlan& pl, const KOp& op_in, const float2* dk, c
 
 template <int N>
 static void lpt3_impl(const FFTPlan& pl, const KOp& op_in, const float2* phi1, const float2* phi2,
-                      float2* const work[3], float* out3, hipStream_t s) {
+                      int terms, int64_t coef_stride, float2* const work[3], float* out3,
+                      hipStream_t s) {
   const int n = pl.n, P = pl.pitch;
   KOp op = op_in;
   op.n = n;
@@ -1689,11 +1702,12 @@ static void lpt3_impl(const FFTPlan& pl, const KOp& op_in, const float2* phi1, c
   {
     ProfScope ps("lpt_fft_x_inv", s);
     constexpr int B = LptXCfg<N>::B;
-    hipLaunchKernelGGL((k_fft_col_lpt<N>), dim3((unsigned)((int64_t)n * P / B)),
-                       dim3(LptXCfg<N>::T), 0, s, phi1, phi2, work[0], work[1], pl.plane, pl.tw, op);
+    hipLaunchKernelGGL((k_fft_col_lpt<N>), dim3((unsigned)(terms * ((int64_t)n * P / B))),
+                       dim3(LptXCfg<N>::T), 0, s, phi1, phi2, work[0], work[1], pl.plane, pl.tw, op,
+                       terms, coef_stride);
     COLA_LAUNCH_CHECK();
   }
-  grad3_tail<N>(pl, op, work, out3, true, s);
+  grad3_tail<N>(pl, op, work, out3, true, s, terms);
 }
 
 template <int N>
@@ -1755,10 +1769,10 @@ void fft_c2r_force3(const FFTPlan& pl, const KOp& op, const float2* dk, const fl
   }
 }
 
-void fft_c2r_lpt3(const FFTPlan& pl, const KOp& op, const float2* phi1, const float2* phi2,
-                  float2* const work[3], float* out3, hipStream_t s) {
+void fft_c2r_lpt3(const FFTPlan& pl, const KOp& op, const float2* phi1, const float2* phi2, int terms,
+                  int64_t coef_stride, float2* const work[3], float* out3, hipStream_t s) {
   switch (pl.n) {
-#define CASE(N_) case N_: lpt3_impl<N_>(pl, op, phi1, phi2, work, out3, s); return;
+#define CASE(N_) case N_: lpt3_impl<N_>(pl, op, phi1, phi2, terms, coef_stride, work, out3, s); return;
     CASE(8) CASE(12) CASE(16) CASE(24) CASE(32) CASE(48) CASE(64) CASE(96) CASE(128)
     CASE(192) CASE(256) CASE(384) CASE(512) CASE(768) CASE(1024) CASE(1536) CASE(2048)
 #undef CASE

@@ -101,6 +101,7 @@ struct Layout {
   // (3 N floats each), over slots 0-2 when they fit there (they are written after the
   // force mesh and read with it by the gather), else in an area of their own.
   size_t off_mesh[6], off_lptw[3], off_lpp3, off_dlt3, work_bytes;
+  int lpt_terms;            // LPT terms transformed together (2, or 1 where memory is short)
   // binned deposit: tile edge (cells), tiles per axis, tile count, and the offsets of
   // the per-tile counters and of the particle-index list sorted by home tile
   int tile, nt1;
@@ -279,8 +280,10 @@ void fft_c2r_force3(const FFTPlan& pl, const KOp& op, const float2* dk, const fl
 // pass forms the field from phi1 and phi2 and writes its two X transforms into work[0]
 // and work[1] (none may alias phi1 or phi2), then the Y and Z passes of fft_c2r_force3
 // write the interleaved rows out3[((x n + y) n + z) 3 + c].  op needs kf, scale and coef.
-void fft_c2r_lpt3(const FFTPlan& pl, const KOp& op, const float2* phi1, const float2* phi2,
-                  float2* const work[3], float* out3, hipStream_t s);
+// `terms` (1 or 2) terms at once: coefficients coef_stride apart, work fields (of n planes)
+// and outputs (of 3 n^3 floats) one behind the other.
+void fft_c2r_lpt3(const FFTPlan& pl, const KOp& op, const float2* phi1, const float2* phi2, int terms,
+                  int64_t coef_stride, float2* const work[3], float* out3, hipStream_t s);
 // Screened source in Fourier space.  dk holds the density contrast after the forward Z
 // and Y passes: one X pass completes delta_k (written back in place for K_POT, where the
 // force needs it; not kept for K_SMOOTH) and applies `kind` (K_POT: Newtonian potential
