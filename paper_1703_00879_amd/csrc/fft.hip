@@ -563,7 +563,7 @@ k_fft_col(float2* __restrict__ data, int64_t elemStride, int64_t tilesPerBlock,
 
 // Forward X pass that bins the power of its modes into shells instead of writing them: the
 // field is read once where a plain pass and a binning kernel read it twice and wrote it
-// once (at n = 1024, 4.3 GB instead of 12.9: 1.8 ms, before 2.3 + 3.2; at 256 22 us, before 23 + 58).  A mode's term
+// once (at n = 1024, 4.3 GB instead of 12.9: 1.6 ms, before 2.3 + 3.2; at 256 22 us, before 23 + 58).  A mode's term
 // w vol (a_r^2 + a_i^2), a = delta_k / (n^3 W), is formed in FP32 in the transform's last stage
 // and added to the block's shell sums in LDS in FP64.  The lanes of a wave hold B adjacent
 // nu_z and a few adjacent nu_x, which meet few shells; where LDS leaves room, every kCopy-th
@@ -613,7 +613,7 @@ k_fft_col_pk(const float2* __restrict__ data, int64_t elemStride, int ntiles,
     const float wy = a.wtab[ny < 0 ? -ny : ny], wz = a.wtab[iz <= h ? iz : 0];
     const unsigned w = (iz > 0 && iz < h) ? 2u : 1u;
     const ColTile<N, B, E, O> io(base, es, tid);
-    auto load = [&](int i, int r, int, int) -> float2 { return load_stream(io.first(data, i, r)); };
+    auto load = [&](int i, int r, int, int) -> float2 { return *io.first(data, i, r); };
     auto store = [&](int j, int c, float2 v, int i, int r) {
       const int nx = j < h ? j : j - N;
       const int n2 = __mul24(nx, nx) + n2yz;
@@ -837,7 +837,10 @@ k_fft_col_inv_yz(const float2* data, float2* outA, float2* __restrict__ outB, in
 // registers from one read of each potential, and two X transforms go out through the LDS
 // tile, as in k_fft_col_fwd_force: G0 = X^-1[-i k_x A] (= X^-1[i k_x (c1 phi1 + c2 phi2)]/N)
 // into o0 and G = X^-1[A] into o1, from which the Y passes of the force transforms give
-// the three components.  Columns past z = n/2 (row padding) get zeros.  With two terms the
+// the three components.  The fields go through the caches: the Y passes find the results
+// there, and 8-column tiles leave half lines that the next tile completes (512^3 pair 2.07
+// -> 1.82 ms against streaming accesses; 256^3 no change, its two-component Y pass 81 -> 72 us).
+// Columns past z = n/2 (row padding) get zeros.  With two terms the
 // second has its coefficients coef_stride further on and its fields behind the first's.
 template <int N>
 struct LptXCfg {
@@ -886,7 +889,7 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
       const int jj = j + r * (N / R0);
-      const float2 a = load_stream(io.first(phi1, i, r)), b = load_stream(io.first(phi2, i, r));
+      const float2 a = *io.first(phi1, i, r), b = *io.first(phi2, i, r);
       const int nx = jj < h ? jj : jj - n;
       const int n2 = nx * nx + n2yz;
       g[i][r] = make_float2(0.f, 0.f);
@@ -902,7 +905,7 @@ k_fft_col_lpt(const float2* __restrict__ phi1, const float2* __restrict__ phi2,
     auto load = [&](int i, int r, int jj, int) -> float2 {
       return t == 0 ? grad_minus_i(op, jj, iy, iz, 0, g[i][r]) : g[i][r];
     };
-    auto store = [&](int, int, float2 v, int i, int r) { store_stream(io.last(out, i, r), v); };
+    auto store = [&](int, int, float2 v, int i, int r) { *io.last(out, i, r) = v; };
     GStages<N, +1, E, B, B, 1, 0, 1, kStoreIR>::run(lds, tid, T, tw, load, store);
     __syncthreads();   // the second transform reuses the LDS tile
   }
