@@ -716,8 +716,8 @@ k_fft_col_fwd_op(float2* __restrict__ data, float2* __restrict__ out, int64_t el
 // the X transform and only two X transforms are needed, G0 = X^-1[-i k_x g] into o0 and
 // G = X^-1[g] into o1; the Y pass forms the y and z components from G.  The outputs may
 // alias dk and src: every read of a column precedes the first write to it.  The column
-// data is touched once, so it streams past the caches and leaves the L2 to the register
-// spills of the two inverse transforms.
+// data is touched once, so it streams past the caches (ordinary accesses: 384^3 8 %, 512^3 10 to
+// 14 % slower, the same at 1024^3).
 template <int N, bool DK>
 __global__ void __launch_bounds__((FusedCfg<N, ColCfg<N>::B>::T))
 k_fft_col_fwd_force(const float2* dk, const float2* src, float2* o0, float2* o1,
