@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "internal.h"
 
@@ -231,10 +232,13 @@ __device__ __forceinline__ void growth_model(const GrowthDev& g, const MBSpline&
 // on a whole table from z = 19: LCDM, 10 slices, 6.5 -> 0.08 ms (0.24 with the divisions of
 // the mode terms, which one mode at k = 0 does not need), against
 // fourth-order Runge-Kutta steps of 1e-3 that evaluated the model in full for every mode
-// and stage.  Steps of 0.04 hold the largest relative error of any table entry at 1e-13 (the
-// Runge-Kutta steps: 4e-13, 9e-12 for the symmetron); it is truncation from 0.05 on, rounding
-// below.  f(R) modes keep the Runge-Kutta steps (further below).
+// and stage.  Steps of 0.04 hold the largest relative error of any LCDM, nDGP or symmetron
+// entry at 1e-13 (the Runge-Kutta steps: 4e-13, 9e-12 for the symmetron); it is truncation
+// from 0.05 on, rounding below.  Models whose coefficients vary faster take the shorter steps
+// of growth_step_bound().  f(R) modes keep the Runge-Kutta steps (further below).
 constexpr double kGrowthStep = 0.04;     // longest step in ln a
+constexpr double kGrowthFloor = 5e-4;    // no step bound is below this, half a Runge-Kutta step,
+constexpr int kGrowthFine = 20000;       // nor below the range of ln a over this number
 constexpr double kGradeFirst = 1e-10;    // after a_*: steps kGradeFirst + kGrade (ln a - ln a_*)
 constexpr double kGrade = 0.1;           // (error 3e-13; 0.2 gives 7e-13, 0.3 1e-11)
 constexpr int kGrowthNodes = 13;         // points of a step: 0 ... 7/8 of the sequences, and 1
@@ -706,11 +710,6 @@ k_growth_fr(GrowthDev g, SpecDev sp, const FrPoint* __restrict__ pts, double* __
   if (wave == 0) integrate(turn - 1, m_prev, h_prev, slice_prev);
 }
 
-// Step boundaries in ln a: every a_i, the knots of a tabulated {m, beta} model (the splines'
-// third derivatives jump there) and the symmetron's a_* are boundaries.  Just after a_*
-// the symmetron's gamma_2 term has a peak whose width in ln a scales as (k / (a_* m_*))^2,
-// far below kGrowthStep for the fundamental mode of a large box, so the steps there start
-// at kGradeFirst and grow by kGrade per step.
 static SpecDev spec_dev(const cola_params& p) {
   SpecDev e;
   const double omh2 = p.omega_m * p.h * p.h, obh2 = p.omega_b * p.h * p.h;
@@ -726,10 +725,117 @@ static SpecDev spec_dev(const cola_params& p) {
   return e;
 }
 
+// Range of ln a a run integrates over (at most that of a double, whose largest has ln 710).
+static double growth_span(const cola_params& p) { return std::min(std::log1p(p.z_init), 710.0); }
+
+static double growth_floor(const cola_params& p) {
+  return std::max(kGrowthFloor, growth_span(p) / kGrowthFine);
+}
+
+// Longest step from l0 to l1 (no knot of a tabulated model between them).  The steps converge
+// like a power series in the step over the distance to the nearest pole of the
+// coefficients in the complex plane: at pi / s for a logistic term of log-slope s, such as
+// k^2/(k^2 + m) with s = |d ln m / d ln a| at whatever k.  So a step takes 0.3 / s at
+// most, and 0.2 / lambda, lambda^2 = 3/2 mu being the largest rate of the growth equation.  A
+// spline piece is also cut in six: beta may rise from 0 to 1 within one.  Measured against
+// steps of 1e-3 (z = 19): k-Mouflage with s = 42 and 84, 1e-8 and 2e-6 with steps of
+// 0.04, 3e-13 now (Runge-Kutta steps of 1e-3: 2e-11 and 3e-11); tables of m^2 ~ a^-40 and a^-80,
+// 6e-8 and 3e-5, now 3e-13 (3e-11 and 7e-10); beta from 0 to 1 over 0.05, 6e-10, now 3e-13 (4e-11).
+// f(R) (s <= 7) and nDGP (s <= 3, mu <= 4/3) stay at kGrowthStep, and so does the symmetron
+// for beta_* <= 2.8, whose slope the graded steps after a_* follow.
+static double growth_step_bound(const cola_params& p, int model, const MBSpline& mb, double l0, double l1) {
+  double slope = 0.0, mu = 1.0, piece = 1.0;   // piece: length of the spline piece
+  if (model == COLA_KMOUFLAGE) {   // P_X - 1 ~ a^{n (m - 1)}
+    slope = std::fabs(p.km_xn) * (p.km_m - 1);
+    mu += 2.0 * p.km_beta * p.km_beta;
+  } else if (model == COLA_SYMMETRON) {
+    mu += 2.0 * p.sym_beta * p.sym_beta;
+  } else if (model == COLA_MBETA) {   // m = a^2 m^2
+    int j = 0;
+    while (j + 2 < mb.n && mb.x[j + 1] <= l0) ++j;
+    const double x0 = mb.x[j], x1 = mb.x[j + 1], h = x1 - x0, M0 = mb.Mm[j], M1 = mb.Mm[j + 1];
+    auto at = [&](double x) {
+      const double u = x1 - x, t = x - x0;
+      slope = std::max(slope, std::fabs(2.0 + (mb.ym[j + 1] - mb.ym[j]) / h - M0 * u * u / (2.0 * h) +
+                                        M1 * t * t / (2.0 * h) - h * (M1 - M0) / 6.0));
+    };
+    at(l0);
+    at(l1);
+    const double xe = x0 + h * M0 / (M0 - M1);   // where the slope is extreme
+    if (xe > l0 && xe < l1) at(xe);
+    const double b = std::max(std::fabs(mb.yb[j]), std::fabs(mb.yb[j + 1])) +
+                     h * h / 8.0 * std::max(std::fabs(mb.Mb[j]), std::fabs(mb.Mb[j + 1]));
+    mu += 2.0 * b * b;
+    piece = h;
+  }
+  double bound = kGrowthStep;
+  if (0.3 < bound * slope) bound = 0.3 / slope;
+  if (0.2 < bound * std::sqrt(1.5 * mu)) bound = 0.2 / std::sqrt(1.5 * mu);
+  if (piece < 6.0 * bound) bound = piece / 6.0;
+  return std::max(bound, growth_floor(p));
+}
+
+// The steps of a run.  Boundaries in ln a: every a_i, the knots of a tabulated {m, beta}
+// model (the splines' third derivatives jump there) and the symmetron's a_*.  Just after
+// a_* the symmetron's gamma_2 term has a peak whose width in ln a scales as
+// (k / (a_* m_*))^2, far below kGrowthStep for the fundamental mode of a large box, so the
+// steps there start at kGradeFirst and grow by kGrade per step.
+struct GrowthList {
+  std::vector<double> l;      // boundaries: step j runs from l[j] to l[j + 1]
+  std::vector<int16_t> out;   // the slice written after step j, or -1
+};
+static GrowthList growth_list(const cola_params& p, int model, const MBSpline& mb) {
+  GrowthList g;
+  double lna = std::log(1.0 / (1.0 + p.z_init));
+  g.l.push_back(lna);
+  auto step = [&](double l1, int out) {
+    g.l.push_back(l1);
+    g.out.push_back((int16_t)out);
+  };
+  // [l0, l1] in equal steps; the last one writes slice `out`
+  auto uniform = [&](double l0, double l1, int out) {
+    const double most = growth_step_bound(p, model, mb, l0, l1);
+    const int n = (int)std::max(1.0, std::ceil(std::min(l1 - l0, 710.0) / most));   // a_ini may be 0
+    const double h = (l1 - l0) / n;
+    for (int j = 0; j < n; ++j) step(j + 1 == n ? l1 : l0 + (j + 1) * h, j + 1 == n ? out : -1);
+  };
+  const bool graded = model == COLA_SYMMETRON;
+  const double kink = graded ? std::log(p.sym_astar) : 0.0;
+  for (int i = 1; i <= p.n_steps; ++i) {
+    const double l1 = std::log(a_of_step(p, i));
+    if (model == COLA_MBETA)
+      for (int j = 0; j < mb.n; ++j)
+        if (mb.x[j] > lna && mb.x[j] < l1) {
+          uniform(lna, mb.x[j], -1);
+          lna = mb.x[j];
+        }
+    if (graded && lna < kink && kink < l1) {
+      uniform(lna, kink, -1);
+      lna = kink;
+    }
+    if (graded && lna >= kink) {
+      const double most = growth_step_bound(p, model, mb, lna, l1);
+      for (;;) {
+        const double h = kGradeFirst + kGrade * (lna - kink);
+        if (h >= most || h >= l1 - lna) break;
+        step(lna + h, -1);
+        lna += h;
+      }
+    }
+    uniform(lna, l1, i);
+    lna = l1;
+  }
+  return g;
+}
+
+// Points of the longest list growth_list() can make: every piece between boundaries takes
+// its length over the step bound, rounded up.
 size_t growth_scratch_bytes(const cola_params& p) {
+  const bool steep = p.growth_mode == 0 && (p.model == COLA_KMOUFLAGE || p.model == COLA_SYMMETRON ||
+                                            p.model == COLA_MBETA);
   const double graded = std::log(kGrowthStep / kGradeFirst) / std::log1p(kGrade);
-  const double span = std::min(std::log1p(p.z_init), 710.0);   // ln of the largest double
-  const double steps = span / kGrowthStep + p.n_steps + COLA_MBETA_MAX_KNOTS + graded + 8;
+  const double steps = growth_span(p) / (steep ? growth_floor(p) : kGrowthStep) + p.n_steps +
+                       COLA_MBETA_MAX_KNOTS + graded + 8;
   return (size_t)steps * kGrowthNodes * sizeof(GrowthNode);
 }
 
@@ -767,57 +873,20 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
   }
   const MBSpline mb = mb_spline(p);
   GrowthNode* nodes = static_cast<GrowthNode*>(scratch);
-  int nsteps = 0;
-  GrowthSteps st;
-  st.n = st.first = 0;
-  auto flush = [&] {
-    if (st.n == 0) return;
+  const GrowthList list = growth_list(p, g.model, mb);
+  const int nsteps = (int)list.out.size();
+  if ((size_t)nsteps * kGrowthNodes * sizeof(GrowthNode) > L.scratch_bytes)
+    throw Error{COLA_E_SIZE, "growth table steps exceed their scratch area"};
+  for (int first = 0; first < nsteps; first += kGrowthChunk) {
+    GrowthSteps st;
+    st.n = std::min(kGrowthChunk, nsteps - first);
+    st.first = first;
+    std::copy_n(list.l.begin() + first, st.n + 1, st.l);
+    std::copy_n(list.out.begin() + first, st.n, st.out);
     const int e = st.n * kGrowthNodes;
     hipLaunchKernelGGL(k_growth_nodes, dim3((e + 63) / 64), dim3(64), 0, s, g, mb, st, nodes);
     COLA_LAUNCH_CHECK();
-    st.first += st.n;
-    st.n = 0;
-  };
-  auto step = [&](double l0, double l1, int out) {
-    st.l[st.n] = l0;
-    st.l[st.n + 1] = l1;
-    st.out[st.n++] = (int16_t)out;
-    ++nsteps;
-    if (st.n == kGrowthChunk) flush();
-  };
-  // [l0, l1] in equal steps of at most kGrowthStep; the last one writes slice `out`
-  auto uniform = [&](double l0, double l1, int out) {
-    const int n = (int)std::min(std::max(1.0, std::ceil((l1 - l0) / kGrowthStep)), 710.0 / kGrowthStep);
-    const double h = (l1 - l0) / n;
-    for (int j = 0; j < n; ++j)
-      step(l0 + j * h, j + 1 == n ? l1 : l0 + (j + 1) * h, j + 1 == n ? out : -1);
-  };
-  const double kink = g.model == COLA_SYMMETRON ? std::log(p.sym_astar) : 0.0;
-  const bool graded = g.model == COLA_SYMMETRON;
-  double lna = std::log(g.a_ini);
-  for (int i = 1; i <= p.n_steps; ++i) {
-    const double l1 = std::log(a_of_step(p, i));
-    if (g.model == COLA_MBETA)
-      for (int j = 0; j < mb.n; ++j)
-        if (mb.x[j] > lna && mb.x[j] < l1) {
-          uniform(lna, mb.x[j], -1);
-          lna = mb.x[j];
-        }
-    if (graded && lna < kink && kink < l1) {
-      uniform(lna, kink, -1);
-      lna = kink;
-    }
-    if (graded && lna >= kink)
-      for (;;) {
-        const double h = kGradeFirst + kGrade * (lna - kink);
-        if (h >= kGrowthStep || h >= l1 - lna) break;
-        step(lna, lna + h, -1);
-        lna += h;
-      }
-    uniform(lna, l1, i);
-    lna = l1;
   }
-  flush();
   const dim3 grid((unsigned)((L.n_k + 1 + 63) / 64) + 1), block(64);
   const bool half = (p.readings & COLA_READ_D2_HALF_K) != 0;
   auto* kernel = half ? (g.kdep ? k_growth_ode<true, true> : k_growth_ode<true, false>)
