@@ -543,7 +543,14 @@ struct FrPlan {
 };
 // points of both integrations: the bound off() takes at the end, twice over a's range
 static int64_t fr_points(const cola_params& p) {
-  return 4 * (int64_t)(std::min(std::log1p(p.z_init), 710.0) / 1e-3) + 6 * ((int64_t)p.n_steps + 4);
+  return 4 * (int64_t)(std::log1p(p.z_init) / 1e-3) + 6 * ((int64_t)p.n_steps + 4);
+}
+// The runs that take these steps.  Before ln a = -40 the gamma_2 term leaves the range of a double
+// (it is not a number with either solver), so no usable run lies beyond the limit, which bounds
+// the points (27 MB).
+static bool fr_pipeline(const cola_params& p) {
+  return p.model == COLA_FR_HS1 && p.growth_mode == 0 && !(p.readings & COLA_READ_D2_HALF_K) &&
+         std::log1p(p.z_init) <= 64.0;
 }
 __device__ __forceinline__ int64_t fr_ref_base(const FrPlan& pl) {   // the reference's points follow
   return 2 * ((int64_t)((log(1.0) - pl.l0) / 1e-3)) + 6 * ((int64_t)pl.n_steps + 2);
@@ -828,9 +835,10 @@ static GrowthList growth_list(const cola_params& p, int model, const MBSpline& m
   return g;
 }
 
-// Points of the longest list growth_list() can make: every piece between boundaries takes
-// its length over the step bound, rounded up.
+// The points of f(R) modes, or of the longest list growth_list() can make: every piece between
+// boundaries takes its length over the step bound, rounded up.
 size_t growth_scratch_bytes(const cola_params& p) {
+  if (fr_pipeline(p)) return (size_t)fr_points(p) * sizeof(FrPoint);
   const bool steep = p.growth_mode == 0 && (p.model == COLA_KMOUFLAGE || p.model == COLA_SYMMETRON ||
                                             p.model == COLA_MBETA);
   const double graded = std::log(kGrowthStep / kGradeFirst) / std::log1p(kGrade);
@@ -861,9 +869,7 @@ void launch_growth_ode(const cola_params& p, const Layout& L, double* table, dou
   g.n_steps = p.n_steps;
   g.n_k = L.n_k;
   const SpecDev sp = spec_dev(p);
-  const size_t fr_bytes = (size_t)fr_points(p) * sizeof(FrPoint);
-  if (g.kdep && g.model == COLA_FR_HS1 && !(p.readings & COLA_READ_D2_HALF_K) &&
-      fr_bytes <= L.scratch_bytes) {
+  if (fr_pipeline(p)) {
     FrPoint* pts = static_cast<FrPoint*>(scratch);
     hipLaunchKernelGGL(k_growth_fr_points, dim3(p.n_steps + 2, 16), dim3(256), 0, s, g, pts);   // + reference
     const dim3 grid((unsigned)((L.n_k + 63) / 64) + 2), block(256);   // + reference, spectrum
