@@ -59,13 +59,18 @@ def secondary_params(C):
 def algorithmic_bytes(name, p):
     """Bytes a kernel must move per launch (single-precision fields, unpadded):
     mesh M = n^3 real cells, half-complex H = n^2 (n/2 + 1) complex values, N particles,
-    and on the particle grid (the LPT transforms) Hp = np^2 (np/2 + 1)."""
+    and on the particle grid (the LPT transforms) Hp = np^2 (np/2 + 1).  A step transforms its
+    two LPT terms in one launch of each pass (t = 2) where mesh slots 0-2 hold both, i.e. on
+    meshes of at least 2 np, up to 768^3 particles."""
     n = p.nmesh1d
     M = n ** 3
     H = n * n * (n // 2 + 1)
     N = p.np1d ** 3
     Hp = p.np1d ** 2 * (p.np1d // 2 + 1)
+    t = 2 if n >= 2 * p.np1d and p.np1d <= 768 else 1
     table = {
+        # the ranks that the count writes for the scatter (4 bytes a particle each way) are
+        # this sort's own and not among the bytes that a binning must move
         "bin_count": 12 * N,                         # read u; tile counts are negligible
         "bin_scan": 0,
         "bin_scatter": 12 * N + 12 * N,              # read u, write one 12-byte record each
@@ -81,10 +86,10 @@ def algorithmic_bytes(name, p):
         "fft_y_inv_yz": 8 * H + 16 * H,              # read G; write the y and z components
         "fft_c2r_z3": 24 * H + 12 * M,               # read 3 force passes, write (Fx, Fy, Fz)
         "gather_kick_drift": 12 * M + 72 * N,        # force mesh; u, v and the LPT terms in; u, v out
-        "lpt_fft_x_inv": 16 * Hp + 16 * Hp,          # read phi1_k, phi2_k; write G0 and G
-        "lpt_fft_y_inv": 16 * Hp,
-        "lpt_fft_y_inv_yz": 8 * Hp + 16 * Hp,
-        "lpt_fft_c2r_z3": 24 * Hp + 12 * N,          # write (x, y, z) of L'' or Delta
+        "lpt_fft_x_inv": 16 * Hp + t * 16 * Hp,      # read phi1_k, phi2_k; write G0 and G
+        "lpt_fft_y_inv": t * 16 * Hp,
+        "lpt_fft_y_inv_yz": t * (8 * Hp + 16 * Hp),
+        "lpt_fft_c2r_z3": t * (24 * Hp + 12 * N),    # write (x, y, z) of L'' or Delta
         "fft_x_inv_lpt": 16 * Hp + 8 * Hp,           # initial conditions: one component
         "lpt_fft_c2r_z": 8 * Hp + 4 * N,
         "fill": 0,
