@@ -133,8 +133,9 @@ struct Dft<8, DIR> {
 // Up to 16 elements: a joined (8, 3) or (8, 4) is compiled to other fused multiply-adds and
 // differs in last digits (lengths 24, 192, 1536 and 2048; with two stages in all, 12 and
 // 24 too, hence three at least).  Gained: 3 to 13 % in the column passes (two-component Y pass
-// of 384^3 154 -> 136 us, of 1024^3 2.84 -> 2.61 ms; force X pass of 1024^3 5.14 -> 4.85 ms)
-// and, with the padded rows, the three-field row pass of 384^3 3.26 -> 2.81 ms.
+// of a 384^3 mesh 154 -> 136 us, of 1024^3 2.84 -> 2.61 ms; force X pass of 1024^3 5.14 ->
+// 4.85 ms) and, with the padded rows, the three-field row pass of 384 complex values (a 768^3
+// mesh) 3.26 -> 2.81 ms.
 template <int N>
 struct Plan;
 #define COLA_PLAN(N_, E_, NST_, ...)                              \

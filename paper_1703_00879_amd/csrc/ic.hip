@@ -387,7 +387,8 @@ struct SpecDev {
 // A with sigma8^2 = A int d ln k k^3/(2 pi^2) k^ns T^2 W(8 k)^2 over 1e-5 < k < 1e2 h/Mpc, by
 // 16-point Gauss-Legendre panels: kSpecLow equal ones in ln k up to kSpecSplit, then kSpecHigh
 // equal ones in k, whose 8 rad of the top-hat's phase each keeps the rule converged (relative
-// error 1e-14).  One wave, a panel node per lane and turn.
+// difference from 4000 panels in ln k 1e-13, 1e-10 for n_s near -3).  One wave, a panel node per
+// lane and turn.
 constexpr int kSpecLow = 64, kSpecHigh = 96;
 constexpr double kSpecSplit = 0.5;
 __device__ __forceinline__ double sigma8_norm(const SpecDev& sp) {
@@ -1058,7 +1059,7 @@ __device__ __forceinline__ float eh_T(const EHDev& e, float k) {
 }
 
 // What turns the white noise into phi1: phi1_k = amp[|nu|^2] W_k, amp = sqrt(N P_ini(k) / L^3) / k^2
-// and 0 at k = 0.  One entry per |nu|^2, a 128th or less of the modes.
+// and 0 at k = 0.  One entry per |nu|^2, about 1.5 / n of the modes.
 struct AmpTable {
   float* amp;
   int n;
